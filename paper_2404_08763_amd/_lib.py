@@ -223,7 +223,7 @@ def calib_activations(layer: Layer, x: torch.Tensor, out: Optional[torch.Tensor]
 def threshold_from_acts(acts: torch.Tensor, sparsity: float, ws: Optional[torch.Tensor] = None) -> float:
     _dev(acts, "acts", torch.float32)
     if ws is None:
-        ws = torch.empty(4096, dtype=torch.uint8, device=acts.device)
+        ws = torch.empty(32768, dtype=torch.uint8, device=acts.device)
     t = _f32()
     _check(raw().cats_threshold_from_acts(_ptr(acts), acts.numel(), float(sparsity), _ptr(ws),
                                           ws.numel(), _stream(), ctypes.byref(t)))

@@ -17,6 +17,7 @@
 //    holding rank r.
 #include "device.hpp"
 #include "internal.hpp"
+#include "scan.hpp"
 
 namespace cats {
 
@@ -228,6 +229,156 @@ hipError_t launch_calib_acts(int wdtype_bf16, const float* x, const void* wg_t, 
   return hipGetLastError();
 }
 
+// ---- select with room for three histograms -------------------------------
+// The r-th smallest |a| by digits of 11, 10 and 10 bits (bits 30..20, 19..10,
+// 9..0), one read of the values per digit.  Each kernel starts by finding
+// the digits before its own in the histograms of the passes before (every
+// block by itself: a scan of a few thousand counters from L2), so a pass is
+// one launch.  Bound by the reads: 4 x 16 bytes in flight per thread.  The
+// first digit is 8 exponent and 3 mantissa bits, so a few dozen bins take
+// most values, and four copies of each counter in neighbouring banks keep a
+// wave's adds apart.  One block of 1024 threads per compute unit: every block
+// adds its bins to the global ones, which costs more than its reads with many
+// blocks.  90 MB (2048 x 11008 values): 16.6 / 17.6 / 16.3 us for the three
+// digits (5.4 TB/s) and 5.6 us for the last kernel, 21.5 / 22.4 / 16.3 with
+// 512 blocks of 512; four 8-bit passes of 4-byte loads took 4 x (42 + 4.5) us.
+constexpr int kSelThreads = 1024;
+constexpr int kSelWaves = kSelThreads / kWaveSize;
+constexpr int kSelBins0 = 2048, kSelBins = 1024;
+constexpr int kSelHist1 = kSelBins0, kSelHist2 = kSelBins0 + kSelBins;
+static_assert(kSelHist2 + kSelBins == kSelectWords, "three histograms");
+
+// The bin of h[0, NB) that holds rank r (1-indexed); r becomes the rank within it.
+template <int NB>
+__device__ __forceinline__ uint32_t find_bin(const uint32_t* __restrict__ h, uint32_t& r, uint32_t* s) {
+  constexpr int PER = NB / kSelThreads;
+  const int tid = threadIdx.x, lane = tid & (kWaveSize - 1), w = tid / kWaveSize;
+  uint32_t c[PER], sum = 0;
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    c[q] = h[tid * PER + q];
+    sum += c[q];
+  }
+  const uint32_t incl = wave_incl_scan(sum);
+  if (lane == kWaveSize - 1) s[w] = incl;
+  __syncthreads();
+  uint32_t before = incl - sum;
+  for (int k = 0; k < w; ++k) before += s[k];
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {  // exactly one bin holds the rank
+    if (before < r && r - before <= c[q]) {
+      s[kSelWaves] = (uint32_t)(tid * PER + q);
+      s[kSelWaves + 1] = r - before;
+    }
+    before += c[q];
+  }
+  __syncthreads();
+  const uint32_t bin = s[kSelWaves];
+  r = s[kSelWaves + 1];
+  __syncthreads();
+  return bin;
+}
+
+template <int PASS>
+__global__ __launch_bounds__(kSelThreads) void k_select_hist(const float* __restrict__ a, int64_t n, uint32_t r,
+                                                             uint32_t* __restrict__ hist) {
+  constexpr int NB = PASS == 0 ? kSelBins0 : kSelBins;
+  constexpr int CP = PASS == 0 ? 4 : 1;  // copies of a counter
+  constexpr int SHIFT = PASS == 0 ? 20 : (PASS == 1 ? 10 : 0);
+  __shared__ uint32_t lh[NB * CP];
+  __shared__ uint32_t s[kSelWaves + 2];
+  const int tid = threadIdx.x;
+  for (int i = tid; i < NB * CP; i += kSelThreads) lh[i] = 0u;
+  uint32_t prefix = 0u, mask = 0x80000000u;  // bit 31 of a key is 0; of an absent one 1
+  if constexpr (PASS >= 1) {
+    prefix = find_bin<kSelBins0>(hist, r, s) << 20;
+    mask |= 0x7ff00000u;
+  }
+  if constexpr (PASS >= 2) {
+    prefix |= find_bin<kSelBins>(hist + kSelHist1, r, s) << 10;
+    mask |= 0x000ffc00u;
+  }
+  __syncthreads();
+  auto count = [&](uint32_t key) {
+    if ((key & mask) == prefix) atomicAdd(&lh[((key >> SHIFT) & (NB - 1)) * CP + (CP > 1 ? (tid & (CP - 1)) : 0)], 1u);
+  };
+  // values before the first and after the last 16-byte boundary: block 0
+  const int64_t head = min(n, (int64_t)(((16u - ((uint32_t)reinterpret_cast<uintptr_t>(a) & 15u)) & 15u) >> 2));
+  const int64_t n4 = (n - head) >> 2, tail = head + 4 * n4;
+  if (blockIdx.x == 0) {
+    if (tid < head) count(__float_as_uint(a[tid]) & 0x7fffffffu);
+    if (tid < n - tail) count(__float_as_uint(a[tail + tid]) & 0x7fffffffu);
+  }
+  const u32x4* a4 = reinterpret_cast<const u32x4*>(a + head);
+  const int64_t stride = (int64_t)gridDim.x * kSelThreads;
+  for (int64_t i = (int64_t)blockIdx.x * kSelThreads + tid; i < n4; i += 4 * stride) {
+    u32x4 v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      v[k] = i + k * stride < n4 ? a4[i + k * stride] : u32x4{~0u, ~0u, ~0u, ~0u};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const uint32_t m = i + k * stride < n4 ? 0x7fffffffu : ~0u;
+      count(v[k].x & m);
+      count(v[k].y & m);
+      count(v[k].z & m);
+      count(v[k].w & m);
+    }
+  }
+  __syncthreads();
+  uint32_t* out = hist + (PASS == 0 ? 0 : (PASS == 1 ? kSelHist1 : kSelHist2));
+  for (int i = tid; i < NB; i += kSelThreads) {
+    uint32_t c = 0;
+#pragma unroll
+    for (int q = 0; q < CP; ++q) c += lh[i * CP + q];
+    if (c) atomicAdd(&out[i], c);
+  }
+}
+
+__global__ __launch_bounds__(kSelThreads) void k_select_pick(const uint32_t* __restrict__ hist, uint32_t r,
+                                                             uint32_t* __restrict__ t) {
+  __shared__ uint32_t s[kSelWaves + 2];
+  uint32_t bits = find_bin<kSelBins0>(hist, r, s) << 20;
+  bits |= find_bin<kSelBins>(hist + kSelHist1, r, s) << 10;
+  bits |= find_bin<kSelBins>(hist + kSelHist2, r, s);
+  if (threadIdx.x == 0) *t = bits;
+}
+
+__global__ __launch_bounds__(kSelThreads) void k_select_clear(uint32_t* hist) {
+  for (int i = threadIdx.x; i < kSelectWords; i += kSelThreads) hist[i] = 0u;
+}
+
+hipError_t launch_select(const float* a, int64_t n, int64_t r, uint32_t* hist, bool clear, uint32_t* t, hipStream_t s) {
+  int64_t blocks = (n + kSelThreads * 16 - 1) / (kSelThreads * 16);
+  if (blocks > 256) blocks = 256;
+  const dim3 grid((unsigned)blocks), block(kSelThreads);
+  hipError_t e;
+  if (clear) {
+    KernelTimer timer("select_clear", s);
+    hipExtLaunchKernelGGL(k_select_clear, dim3(1), block, 0, s, timer.start(), timer.stop(), 0, hist);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  {
+    KernelTimer timer("select_hist0", s);
+    hipExtLaunchKernelGGL(k_select_hist<0>, grid, block, 0, s, timer.start(), timer.stop(), 0, a, n, (uint32_t)r, hist);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  {
+    KernelTimer timer("select_hist1", s);
+    hipExtLaunchKernelGGL(k_select_hist<1>, grid, block, 0, s, timer.start(), timer.stop(), 0, a, n, (uint32_t)r, hist);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  {
+    KernelTimer timer("select_hist2", s);
+    hipExtLaunchKernelGGL(k_select_hist<2>, grid, block, 0, s, timer.start(), timer.stop(), 0, a, n, (uint32_t)r, hist);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  KernelTimer timer("select_pick", s);
+  hipExtLaunchKernelGGL(k_select_pick, dim3(1), block, 0, s, timer.start(), timer.stop(), 0, hist, (uint32_t)r, t);
+  return hipGetLastError();
+}
+
+// ---- select in a scratch of 260 words (a workspace sized for less) --------
 // scratch layout: [0, 256) histogram, [256] selected prefix, [257..258]
 // remaining rank (low, high word).
 constexpr int kRadixPrefix = 256;

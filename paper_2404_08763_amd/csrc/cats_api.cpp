@@ -122,6 +122,22 @@ size_t calib_bytes(int64_t nvalues) {
   return radix_bytes() + round_up((size_t)nvalues * sizeof(float), kAlign);
 }
 
+// bf16 planes of N vectors of k values (gemm_rows.hip).
+size_t planes_bytes(int ns, int64_t N, int k) {
+  return round_up((size_t)ns * (size_t)N * (size_t)cats::rows_kp(k) * sizeof(uint16_t), kAlign);
+}
+
+// Histograms of the one-read-per-digit select and the bit patterns it finds.
+size_t select_bytes(int results) { return round_up((size_t)(cats::kSelectWords + results) * sizeof(uint32_t), kAlign); }
+
+// calib_bytes with, behind the activations, room for the calibration vectors'
+// planes (so that they are split once and not by every block of the gate
+// product) and the select's histograms.  A workspace without it (calib_bytes)
+// is still accepted.
+size_t calib_planes_bytes(int d, int64_t N, int64_t nvalues) {
+  return calib_bytes(nvalues) + planes_bytes(2, N, d) + select_bytes(1);
+}
+
 bool d_ok(int32_t d, int32_t wdtype) {
   if (d <= 0 || d % 8 != 0) return false;
   return d <= (wdtype == CATS_BF16 ? CATS_MAX_D_BF16 : CATS_MAX_D_F32);
@@ -322,18 +338,22 @@ int64_t cutoff_rank(int64_t n, double k) {
   return (int64_t)r;
 }
 
-cats_status select_threshold(const float* acts, int64_t n, double k, void* ws, hipStream_t s,
+// The cutoff of n activations through `wide` (select_bytes(1) bytes,
+// histograms cleared when `clear`) or, where the workspace is too small for it
+// (wide NULL), through the 260 words at ws.
+cats_status select_threshold(const float* acts, int64_t n, double k, void* ws, void* wide, bool clear, hipStream_t s,
                              float* t_out) {
   const int64_t r = cutoff_rank(n, k);
   if (r == 0) {
     *t_out = 0.f;
     return CATS_OK;
   }
-  uint32_t* sc = static_cast<uint32_t*>(ws);
-  hipError_t e = cats::launch_radix_select(acts, n, r, sc, s);
+  uint32_t* sc = static_cast<uint32_t*>(wide ? wide : ws);
+  uint32_t* found = sc + (wide ? cats::kSelectWords : 256);
+  hipError_t e = wide ? cats::launch_select(acts, n, r, sc, clear, found, s) : cats::launch_radix_select(acts, n, r, sc, s);
   if (e != hipSuccess) return hip_fail(e, "radix select launch");
   uint32_t bits = 0;
-  e = hipMemcpyAsync(&bits, sc + 256, sizeof(bits), hipMemcpyDeviceToHost, s);
+  e = hipMemcpyAsync(&bits, found, sizeof(bits), hipMemcpyDeviceToHost, s);
   if (e != hipSuccess) return hip_fail(e, "threshold copy");
   e = hipStreamSynchronize(s);
   if (e != hipSuccess) return hip_fail(e, "stream synchronize");
@@ -400,6 +420,22 @@ hipEvent_t timer_event_locked(TimerState& T) {
   hipEvent_t e = nullptr;
   if (hipEventCreate(&e) != hipSuccess) return nullptr;
   return e;
+}
+
+// The gate product of N vectors given as planes.
+cats::RowsGemmArgs gate_rows(const cats_layer* L, const uint16_t* xs, int N, float* acts) {
+  cats::RowsGemmArgs ga{};
+  ga.w0 = L->w_gate_t;
+  ga.w1 = L->w_up_t;
+  ga.xs = xs;
+  ga.N = N;
+  ga.wrows = L->m;
+  ga.wcols = L->d;
+  ga.K = L->d;
+  ga.Kp = cats::rows_kp(L->d);
+  ga.S = 1;
+  ga.out = acts;
+  return ga;
 }
 
 }  // namespace
@@ -472,7 +508,8 @@ size_t cats_workspace_bytes(int32_t d, int32_t m, int32_t max_batch, int64_t max
       max_batch > CATS_MAX_BATCH || max_calib_values < 0)
     return 0;
   const size_t fwd = fwd_layout(d, m, max_batch).end + stack_rows_bytes(d, max_batch);
-  const size_t cal = calib_bytes(max_calib_values);
+  const size_t cal = max_calib_values == 0 ? calib_bytes(0)
+                                           : calib_planes_bytes(d, (max_calib_values + m - 1) / m, max_calib_values);
   return fwd > cal ? fwd : cal;
 }
 
@@ -518,7 +555,8 @@ cats_status cats_threshold_from_acts(const float* acts, int64_t n, double sparsi
   }
   cats_status st = check_ws(ws, ws_bytes, radix_bytes());
   if (st != CATS_OK) return st;
-  return select_threshold(acts, n, sparsity, ws, static_cast<hipStream_t>(stream), t_out);
+  return select_threshold(acts, n, sparsity, ws, ws_bytes >= select_bytes(1) ? ws : nullptr, true,
+                          static_cast<hipStream_t>(stream), t_out);
 }
 
 cats_status cats_calibrate_threshold(const cats_layer* layer, const float* calib_x, int32_t N,
@@ -541,10 +579,32 @@ cats_status cats_calibrate_threshold(const cats_layer* layer, const float* calib
   if (st != CATS_OK) return st;
   float* acts = reinterpret_cast<float*>(static_cast<char*>(ws) + radix_bytes());
   const hipStream_t s = static_cast<hipStream_t>(stream);
-  hipError_t e = cats::launch_calib_acts(layer->wdtype == CATS_BF16, calib_x, layer->w_gate_t, N,
-                                         layer->d, layer->m, acts, s);
+  hipError_t e;
+  if (ws_bytes < calib_planes_bytes(layer->d, N, n)) {
+    e = cats::launch_calib_acts(layer->wdtype == CATS_BF16, calib_x, layer->w_gate_t, N, layer->d, layer->m, acts, s);
+    if (e != hipSuccess) return hip_fail(e, "calibration activations launch");
+    return select_threshold(acts, n, sparsity, ws, nullptr, true, s, t_out);
+  }
+  char* planes = static_cast<char*>(ws) + calib_bytes(n);
+  uint32_t* hist = reinterpret_cast<uint32_t*>(planes + planes_bytes(2, N, layer->d));
+  if (layer->wdtype == CATS_BF16) {
+    cats::RowsSplitArgs sa{};
+    sa.x = calib_x;
+    sa.xs = reinterpret_cast<uint16_t*>(planes);
+    sa.N = N;
+    sa.d = layer->d;
+    sa.Kp = cats::rows_kp(layer->d);
+    sa.zero = hist;
+    sa.nzero = cats::kSelectWords;
+    e = cats::launch_rows_split(2, sa, s);
+    if (e != hipSuccess) return hip_fail(e, "calibration vector split launch");
+    cats::RowsGemmArgs ga = gate_rows(layer, sa.xs, N, acts);
+    e = cats::launch_rows_acts(2, ga, s);
+  } else {
+    e = cats::launch_calib_acts(0, calib_x, layer->w_gate_t, N, layer->d, layer->m, acts, s);
+  }
   if (e != hipSuccess) return hip_fail(e, "calibration activations launch");
-  return select_threshold(acts, n, sparsity, ws, s, t_out);
+  return select_threshold(acts, n, sparsity, ws, hist, layer->wdtype != CATS_BF16, s, t_out);
 }
 
 cats_status cats_mlp_forward(const cats_layer* layer, const float* x, int32_t B, float t,
@@ -769,14 +829,106 @@ size_t stack_calib_general(int d, int max_m, int N) {
   const size_t fwd = fwd_layout(d, max_m, CATS_MAX_BATCH).end + stack_rows_bytes(d, CATS_MAX_BATCH);
   return cal > fwd ? cal : fwd;
 }
+
+// Workspace of the many-row propagation: the select scratch and general
+// region of the row-group path (activations, later the down-projection's
+// partial sums, which need one [N x d] at least), X, then the planes of
+// RMSNorm(X) and of h, and the select's histograms and results.
+struct StackCalibLayout {
+  size_t acts_bytes, X, xs, hs, hist, end;
+};
+StackCalibLayout stack_calib_layout(int d, int max_m, int N, int L) {
+  StackCalibLayout o;
+  const size_t rows = round_up((size_t)N * d * sizeof(float), kAlign);
+  size_t general = stack_calib_general(d, max_m, N);
+  if (general < radix_bytes() + rows) general = radix_bytes() + rows;
+  o.acts_bytes = general - radix_bytes();
+  o.X = general;
+  o.xs = o.X + rows;
+  o.hs = o.xs + planes_bytes(3, N, d);
+  o.hist = o.hs + planes_bytes(3, N, max_m);
+  o.end = o.hist + select_bytes(L);
+  return o;
+}
 }  // namespace
 
 size_t cats_calibrate_stack_workspace_bytes(int32_t d, int32_t max_m, int32_t N) {
   if (d <= 0 || d % 8 != 0 || d > CATS_MAX_D_BF16 || max_m <= 0 || max_m > CATS_MAX_M || N <= 0 ||
       N > 4 * 1024 * 1024 || (int64_t)N * max_m > (int64_t)0xffffffffll)
     return 0;
-  return stack_calib_general(d, max_m, N) + 2 * round_up((size_t)N * d * sizeof(float), kAlign);
+  const size_t groups = stack_calib_general(d, max_m, N) + 2 * round_up((size_t)N * d * sizeof(float), kAlign);
+  const size_t many = stack_calib_layout(d, max_m, N, CATS_MAX_LAYERS).end;
+  return many > groups ? many : groups;
 }
+
+namespace {
+// cats_calibrate_stack for bf16 layers and enough vectors: every layer's
+// products take all N vectors in one launch each.  Nothing is read back
+// until the last layer's cutoff is found.
+cats_status calibrate_stack_rows(const cats_layer* layers, int L, const float* calib_x, int N, double sparsity, float eps,
+                                 int ns, const StackCalibLayout& lay, void* ws, hipStream_t s, float* t_out) {
+  char* w = static_cast<char*>(ws);
+  const int d = layers[0].d;
+  float* acts = reinterpret_cast<float*>(w + radix_bytes());  // then the down-projection's partial sums
+  float* X = reinterpret_cast<float*>(w + lay.X);
+  uint16_t* hs = reinterpret_cast<uint16_t*>(w + lay.hs);
+  uint32_t* hist = reinterpret_cast<uint32_t*>(w + lay.hist);
+  cats::RowsSplitArgs sa{};
+  sa.x = calib_x;
+  sa.xs = reinterpret_cast<uint16_t*>(w + lay.xs);
+  sa.N = N;
+  sa.d = d;
+  sa.Kp = cats::rows_kp(d);
+  sa.norm = 1;
+  sa.eps = eps;
+  sa.zero = hist;
+  sa.nzero = cats::kSelectWords;
+  for (int l = 0; l < L; ++l) {
+    const cats_layer* ly = &layers[l];
+    const bool last = l == L - 1;
+    hipError_t e = cats::launch_rows_split(ns, sa, s);
+    if (e != hipSuccess) return hip_fail(e, "calibration vector split launch");
+    if (l > 0) sa.x = X;
+    cats::RowsGemmArgs ga = gate_rows(ly, sa.xs, N, acts);
+    ga.hs = hs;
+    ga.Kp2 = cats::rows_kp(ly->m);
+    e = last ? cats::launch_rows_acts(ns, ga, s) : cats::launch_rows_gateup(ns, ga, s);
+    if (e != hipSuccess) return hip_fail(e, "gate and up products launch");
+    const int64_t n = (int64_t)N * ly->m;
+    e = cats::launch_select(acts, n, cutoff_rank(n, sparsity), hist, false, hist + cats::kSelectWords + l, s);
+    if (e != hipSuccess) return hip_fail(e, "radix select launch");
+    if (last) break;
+    // X <- X + dense MLP_l(RMSNorm(X)): the reduction over the neurons in S
+    // parts, enough for two blocks per compute unit, each at least 16 steps
+    // long; the next split adds them up
+    cats::RowsGemmArgs da{};
+    da.w0 = ly->w_down;
+    da.xs = hs;
+    da.N = N;
+    da.wrows = ly->m;
+    da.wcols = d;
+    da.K = ly->m;
+    da.Kp = ga.Kp2;
+    da.out = acts;
+    const int64_t tiles = (int64_t)((d + cats::kRowsTileM - 1) / cats::kRowsTileM) *
+                          ((N + cats::kRowsTileN - 1) / cats::kRowsTileN);
+    int64_t S = 2 * cats::kFusedBlocks / tiles;
+    const int64_t fit = (int64_t)(lay.acts_bytes / ((size_t)N * d * sizeof(float)));
+    if (S > fit) S = fit;
+    if (S > ga.Kp2 / 512) S = ga.Kp2 / 512;
+    da.S = S < 1 ? 1 : (int)S;
+    e = cats::launch_rows_down(ns, da, s);
+    if (e != hipSuccess) return hip_fail(e, "down-projection launch");
+    sa.partial = acts;
+    sa.S = da.S;
+    sa.xsum = X;
+  }
+  hipError_t e = hipMemcpyAsync(t_out, hist + cats::kSelectWords, (size_t)L * sizeof(float), hipMemcpyDeviceToHost, s);
+  if (e != hipSuccess) return hip_fail(e, "threshold copy");
+  e = hipStreamSynchronize(s);
+  return e == hipSuccess ? CATS_OK : hip_fail(e, "stream synchronize");
+}
+}  // namespace
 
 cats_status cats_calibrate_stack(const cats_layer* layers, int32_t L, const float* calib_x, int32_t N,
                                  double sparsity, float eps, void* ws, size_t ws_bytes, void* stream,
@@ -806,6 +958,15 @@ cats_status cats_calibrate_stack(const cats_layer* layers, int32_t L, const floa
   cats_status st = check_ws(ws, ws_bytes, general + 2 * rows);
   if (st != CATS_OK) return st;
   const hipStream_t s = static_cast<hipStream_t>(stream);
+  // Two planes where the 16-row groups use two in every call; three, all of
+  // fp32's bits, where some group's products run on fp32 x (a width the
+  // matrix-core kernels lack, or a last group below their fewest rows).
+  const int tail_rows = N % CATS_MAX_BATCH;
+  const int ns = cats::batched_ks(d) > 0 && (tail_rows == 0 || tail_rows >= cats::kBatchedMinRows) ? 2 : 3;
+  bool many = true;
+  for (int l = 0; l < L; ++l) many = many && layers[l].wdtype == CATS_BF16;
+  const StackCalibLayout lay = stack_calib_layout(d, max_m, N, L);
+  if (many && ws_bytes >= lay.end) return calibrate_stack_rows(layers, L, calib_x, N, sparsity, eps, ns, lay, ws, s, t_out);
   float* X = reinterpret_cast<float*>(static_cast<char*>(ws) + general);
   float* XN = reinterpret_cast<float*>(static_cast<char*>(ws) + general + rows);
   float* acts = reinterpret_cast<float*>(static_cast<char*>(ws) + radix_bytes());
@@ -818,7 +979,7 @@ cats_status cats_calibrate_stack(const cats_layer* layers, int32_t L, const floa
     if (e != hipSuccess) return hip_fail(e, "rmsnorm launch");
     e = cats::launch_calib_acts(ly->wdtype == CATS_BF16, XN, ly->w_gate_t, N, d, ly->m, acts, s);
     if (e != hipSuccess) return hip_fail(e, "calibration activations launch");
-    st = select_threshold(acts, (int64_t)N * ly->m, sparsity, ws, s, &t_out[l]);
+    st = select_threshold(acts, (int64_t)N * ly->m, sparsity, ws, nullptr, true, s, &t_out[l]);
     if (st != CATS_OK) return st;
     if (l == L - 1) break;
     // X <- X + dense MLP_l(XN), CATS_MAX_BATCH rows per call

@@ -174,12 +174,50 @@ hipError_t launch_gateup(bool dense, bool aux, const BatchedArgs& a, int G, hipS
 hipError_t launch_down_mfma(const DownArgs& a, hipStream_t s);
 hipError_t launch_sparse_input(const SparseInputArgs& a, hipStream_t s);
 
+// Many-row products of the calibration (gemm_rows.hip): x as bf16 planes,
+// one tile of kRowsTileM output rows x kRowsTileN vectors per block.
+constexpr int kRowsTileM = 256, kRowsTileN = 128;
+// Columns of a plane row: the k of whole matrix-core steps.
+inline int rows_kp(int k) { return (k + 31) / 32 * 32; }
+struct RowsSplitArgs {
+  const float* x;         // [N x d]
+  const float* partial;   // [S x N x d] added to x first (S > 0)
+  float* xsum;            // [N x d] receives x + partials, or null (needs S > 0 or equals x)
+  uint16_t* xs;           // [planes x N x Kp]
+  int N, d, Kp, S;
+  int norm;               // planes of RMSNorm(x) (unit gain) instead of x
+  float eps;
+  uint32_t* zero;         // nzero words cleared on the way, or null
+  int nzero;
+};
+struct RowsGemmArgs {
+  const void* w0;         // [wrows x wcols] bf16: W_gate^T (acts, gate/up) or W_down
+  const void* w1;         // W_up^T (gate/up)
+  const uint16_t* xs;     // [planes x N x Kp]
+  int N, wrows, wcols;
+  int K, Kp;              // reduction length: wcols, or wrows for W_down
+  int MT, NT;             // tiles (set by the launcher)
+  int S;                  // parts of the reduction (down only; 1 otherwise)
+  float* out;             // [N x wrows] |v|, or W_down's [S x N x wcols] partial sums
+  uint16_t* hs;           // gate/up: [planes x N x Kp2] planes of h
+  int Kp2;
+};
+hipError_t launch_rows_split(int ns, const RowsSplitArgs& a, hipStream_t s);
+hipError_t launch_rows_acts(int ns, const RowsGemmArgs& a, hipStream_t s);
+hipError_t launch_rows_gateup(int ns, const RowsGemmArgs& a, hipStream_t s);
+hipError_t launch_rows_down(int ns, const RowsGemmArgs& a, hipStream_t s);
+
 hipError_t launch_calib_acts(int wdtype_bf16, const float* x, const void* wg_t, int N, int d,
                              int m, float* acts, hipStream_t s);
 // Radix select of the r-th smallest |a| (1-indexed) over n fp32 values;
 // `scratch` holds 260 words.  The selected bit pattern ends in scratch[256].
 hipError_t launch_radix_select(const float* a, int64_t n, int64_t r, uint32_t* scratch,
                                hipStream_t s);
+
+// The same with `hist` of kSelectWords words (cleared first when `clear`): t
+// receives the selected bit pattern.  n below 2^32.
+constexpr int kSelectWords = 2048 + 2 * 1024;
+hipError_t launch_select(const float* a, int64_t n, int64_t r, uint32_t* hist, bool clear, uint32_t* t, hipStream_t s);
 
 hipError_t launch_rmsnorm(const float* x, float* xn, int B, int d, float eps, hipStream_t s);
 constexpr uint64_t kStreamReadMaxBytes = 1ull << 30;

@@ -1,0 +1,115 @@
+"""Many-row calibration products and the wide select, at the edges of their
+tiles (64 / 128 / 256 output rows, 128 vectors, 32-deep steps) and of the rules
+that choose them, against 64-bit products in plain torch."""
+import math
+
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+EPS = 1e-5
+
+
+def _P():
+    import paper_2404_08763_amd as P
+
+    return P
+
+
+def _layers(d, m, L, seed):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    return [[(torch.randn((m, d), generator=g, device="cuda") * 0.05).bfloat16() for _ in range(3)] for _ in range(L)]
+
+
+def _acts64(x, w):
+    z = x @ w.double().t()
+    return (z / (1 + torch.exp(-z))).abs()
+
+
+def _rank(n, k):
+    return min(max(math.ceil(k * n - 1e-6), 1), n)
+
+
+# 64-row blocks unless m and N give 80 (128 rows) or 170 (256 rows) blocks of 256
+@pytest.mark.parametrize("d,m,N", [
+    (8, 7, 1),          # one partial tile of everything
+    (40, 300, 129),     # one vector and eight channels past a tile
+    (264, 65, 128),     # one neuron past a tile
+    (72, 20500, 100),   # 81 blocks: 128 rows
+    (64, 11000, 513),   # 215 blocks: 256 rows, one vector past a tile
+])
+def test_calibrate_threshold_tiles(d, m, N):
+    P = _P()
+    w = _layers(d, m, 1, 3)[0]
+    x = torch.randn((N, d), generator=torch.Generator(device="cuda").manual_seed(4), device="cuda")
+    layer = P.Layer(*w)
+    ref = _acts64(x.double(), w[0])
+    # each product loses 2^-16 of x at most and the sum d roundings; SiLU' is
+    # below 1.1; an order statistic moves by no more than its values do
+    err = 1.1 * (2.0 ** -16 + d * 2.0 ** -24) * (x.double().abs() @ w[0].double().abs().t()).max().item()
+    small = torch.empty(1280 + (N * m * 4 + 255) // 256 * 256, dtype=torch.uint8, device="cuda")
+    for k in (0.001, 0.5, 0.93, 1.0):
+        want = ref.reshape(-1).sort().values[_rank(N * m, k) - 1].item()
+        got = P.calibrate_threshold(layer, x, k)
+        # a workspace without room for the planes takes the other kernels
+        other = P.calibrate_threshold(layer, x, k, ws=small)
+        assert abs(got - want) <= err + 4e-6 * want
+        assert abs(other - want) <= err + 4e-6 * want
+
+
+@pytest.mark.parametrize("d,m,N,L", [
+    (512, 130, 48, 3),    # two planes
+    (512, 65, 33, 2),     # a last group of one row: three planes
+    (1032, 693, 35, 3),   # a width without 16-row matrix-core kernels: three planes
+    (264, 31, 129, 2),    # fewer neurons than a step is deep
+    (2048, 40, 20, 2),    # d > m: the partial sums outgrow the activations
+    (256, 5500, 520, 2),  # 256-row blocks, the reduction in parts
+])
+def test_calibrate_stack_rows(d, m, N, L):
+    P = _P()
+    ws = _layers(d, m, L, 5)
+    stack = P.Stack([P.Layer(*w) for w in ws])
+    x0 = torch.randn((N, d), generator=torch.Generator(device="cuda").manual_seed(6), device="cuda")
+    got = P.calibrate_stack(stack, x0, 0.5, eps=EPS)
+    x = x0.double()
+    for l, w in enumerate(ws):
+        xn = x / torch.sqrt((x * x).mean(dim=1, keepdim=True) + EPS)
+        a = _acts64(xn, w[0])
+        want = a.reshape(-1).sort().values[_rank(N * m, 0.5) - 1].item()
+        # the bound above, with the stream's own error (the same products, a
+        # few 2^-16 of it) on top: twice as much per layer before
+        err = (1 + 2 * l) * 1.1 * (2.0 ** -16 + d * 2.0 ** -24) * (xn.abs() @ w[0].double().abs().t()).max().item()
+        assert abs(got[l] - want) <= err, (l, got[l], want)
+        z = xn @ w[0].double().t()
+        x = x + ((z / (1 + torch.exp(-z))) * (xn @ w[1].double().t())) @ w[2].double()
+    # the 16-row groups (a workspace of their size) agree within the same error
+    groups = max(1280 + (N * m * 4 + 255) // 256 * 256, P.workspace_bytes(d, m, 16)) + 2 * ((N * d * 4 + 255) // 256 * 256)
+    other = P.calibrate_stack(stack, x0, 0.5, eps=EPS, ws=torch.empty(groups, dtype=torch.uint8, device="cuda"))
+    assert all(abs(a - b) <= 2 * err for a, b in zip(got, other))
+
+
+def test_calibrate_stack_rows_keeps_inf_and_nan():
+    """Three planes: an infinite channel makes what fp32 products make of it."""
+    P = _P()
+    w = _layers(264, 31, 2, 9)
+    x = torch.randn((20, 264), device="cuda")
+    x[3, 5] = float("inf")
+    t = P.calibrate_stack(P.Stack([P.Layer(*v) for v in w]), x, 1.0, eps=EPS)
+    assert all(math.isnan(v) for v in t)  # RMSNorm of an infinity is NaN, the largest bit pattern
+
+
+@pytest.mark.parametrize("n,shift", [(1, 0), (1, 3), (3, 1), (1023, 2), (16384, 0), (16389, 1), (4200003, 3)])
+def test_wide_select_exact(n, shift):
+    P = _P()
+    g = torch.Generator(device="cuda").manual_seed(n)
+    buf = torch.randn(n + 4, generator=g, device="cuda") * torch.exp(3 * torch.randn(n + 4, generator=g, device="cuda"))
+    buf[shift + n // 2] = float("inf")
+    a = buf[shift:shift + n]  # every alignment of the first value
+    s = a.abs().sort().values
+    for k in (1e-9, 0.25, 0.5, 0.999, 1.0):
+        want = s[_rank(n, k) - 1].item()
+        assert P.threshold_from_acts(a, k) == want
+        assert P.threshold_from_acts(a, k, ws=torch.empty(1280, dtype=torch.uint8, device="cuda")) == want
+    same = torch.full((n,), 0.25, device="cuda")
+    assert P.threshold_from_acts(same, 0.5) == 0.25
