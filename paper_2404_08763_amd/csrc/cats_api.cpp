@@ -80,9 +80,11 @@ size_t radix_bytes() { return round_up(kRadixWords * sizeof(uint32_t), kAlign); 
 
 // Neuron groups and column tiles of the batched down-projection.
 int down_ct(int d) { return (d + cats::kDownCols - 1) / cats::kDownCols; }
+// (a block per compute unit, but no group of less than one 32-row step).
 int down_ng(int d, int m) {
   const int G = cats::fused_grid(m);
-  const int ng = cats::kFusedBlocks / down_ct(d);
+  int ng = cats::kFusedBlocks / down_ct(d);
+  if (ng > (m + 32 - 1) / 32) ng = (m + 32 - 1) / 32;
   return ng < 1 ? 1 : (ng > G ? G : ng);
 }
 
@@ -210,38 +212,40 @@ cats_status run_mlp(const cats_layer* L, const float* x, int32_t B, float t, boo
   char* w = static_cast<char*>(ws);
   const hipStream_t s = static_cast<hipStream_t>(stream);
   const int G = cats::fused_grid(m);
-  if (!vin && bf16 && B >= cats::kBatchedMinRows && cats::batched_ks(d) > 0) {
+  const int planes = cats::batch_planes(d, B);
+  if (!vin && bf16 && cats::batched_rows(d, m, B)) {
     // all rows in one pass: gate/up on the matrix cores, down by column tiles
-    cats::BatchedArgs ba;
+    cats::GateUpArgs ba{};
     ba.wg = L->w_gate_t;
     ba.wu = L->w_up_t;
     ba.x = x;
+    ba.norm = norm ? 1 : 0;
+    ba.eps = eps;
     ba.B = B;
     ba.d = d;
     ba.m = m;
     ba.t = dense ? 0.f : t;
-    ba.norm = norm ? 1 : 0;
-    ba.eps = eps;
+    ba.aux = want_aux ? 1 : 0;
     ba.seg_j = reinterpret_cast<int*>(w + lay.seg_j);
     ba.seg_mask = reinterpret_cast<uint32_t*>(w + lay.seg_mask);
     ba.seg_v = reinterpret_cast<float*>(w + lay.seg_v);
     ba.seg_h = reinterpret_cast<float*>(w + lay.seg_h);
     ba.seg_cnt = reinterpret_cast<int*>(w + lay.seg_cnt);
-    hipError_t e = cats::launch_gateup(dense, want_aux, ba, G, s);
+    hipError_t e = cats::launch_gateup(dense, planes, ba, G, s);
     if (e != hipSuccess) return hip_fail(e, "gate/up launch");
     cats::DownArgs da;
     da.wd = L->w_down;
     da.partial = reinterpret_cast<float*>(w + lay.partial);
     da.seg_j = ba.seg_j;
+    da.seg_mask = ba.seg_mask;
     da.seg_h = ba.seg_h;
-    da.seg_cnt = ba.seg_cnt;
     da.B = B;
     da.d = d;
     da.m = m;
     da.G = G;
     da.NG = down_ng(d, m);
     da.CT = down_ct(d);
-    e = cats::launch_down_mfma(da, s);
+    e = cats::launch_down(planes, da, s);
     if (e != hipSuccess) return hip_fail(e, "down-projection launch");
     cats::ReduceArgs ra;
     ra.partial = da.partial;
@@ -461,6 +465,32 @@ int fused_bt_max(int wdtype_bf16, int nch) {
   int bt = kMaxBatchTile;
   while (bt > 1 && bt * row_bytes > kXLdsBytes) bt /= 2;
   return bt;
+}
+
+// Two planes (16 of x's 24 significand bits) where the products have always
+// been taken so: 5 rows or more at the widths of 512 k columns below.  Three
+// (all 24 bits) elsewhere, where fp32 products were.
+static bool two_plane_width(int d) {
+  const int k = d % 512 == 0 ? d / 512 : 0;
+  return k == 1 || k == 2 || k == 4 || k == 6 || k == 8 || k == 10;
+}
+int batch_planes(int d, int B) { return B >= 5 && two_plane_width(d) ? 2 : 3; }
+
+// Whether the matrix-core path (three launches) takes a call, or the fused
+// kernel (two, its products on the vector ALUs).  Up to 4 rows the fused
+// kernel's dot products keep up with the weights (4096 x 11008, k = 0.7, 4
+// rows: 54 us against 58); from 9 rows it reads the weights twice.  In between
+// it is faster only for small narrow blocks, where a launch weighs more than
+// the products (us, fused / matrix cores: 512 x 1408 at 5 rows 12.5 / 15.3, at 8
+// rows 14.6 / 15.3; 1024 x 1024 at 5 rows 15.0 / 17.4; 512 x 3000 at 5 rows
+// 15.4 / 15.8, at 8 rows 18.2 / 16.0; 1024 x 2048 at 6 rows 17.4 / 16.6;
+// 1000 x 3000 at 5 rows 19.2 / 18.0).  At the three-plane widths small blocks
+// keep the fused kernel at every row count: there the forward is bit for bit
+// the separate kernels' result (cats_mlp_forward_unfused).
+bool batched_rows(int d, int m, int B) {
+  if (B < 5) return false;
+  if ((int64_t)B * m * (d < 512 ? 512 : d) > 8000000) return true;
+  return two_plane_width(d) && (B > 8 || d > 1024);
 }
 
 int fused_grid(int m) { return m < kFusedBlocks ? m : kFusedBlocks; }
@@ -962,7 +992,7 @@ cats_status cats_calibrate_stack(const cats_layer* layers, int32_t L, const floa
   // fp32's bits, where some group's products run on fp32 x (a width the
   // matrix-core kernels lack, or a last group below their fewest rows).
   const int tail_rows = N % CATS_MAX_BATCH;
-  const int ns = cats::batched_ks(d) > 0 && (tail_rows == 0 || tail_rows >= cats::kBatchedMinRows) ? 2 : 3;
+  const int ns = cats::batch_planes(d, tail_rows == 0 ? CATS_MAX_BATCH : tail_rows);
   bool many = true;
   for (int l = 0; l < L; ++l) many = many && layers[l].wdtype == CATS_BF16;
   const StackCalibLayout lay = stack_calib_layout(d, max_m, N, L);

@@ -36,29 +36,10 @@ constexpr int kGrXcds = 8;        // block b runs on XCD b mod 8
 
 enum GrMode { kGrActs, kGrGateUp, kGrDown };
 
-// 16 bytes per lane from memory to LDS (lane l's at dst + 16 l).
-__device__ __forceinline__ void dma16(__amdgpu_buffer_rsrc_t r, uint8_t* dst, uint32_t off) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)dst, 16, (int)off, 0, 0, 0);
-}
-
-// Value -> NS bf16 planes.  Two planes: nearest hi, nearest lo (as the other
-// matrix-core paths split).  Three: cut to 8 bits each, whose sum is the value.
 template <int NS>
 __device__ __forceinline__ void split_planes(float f, uint16_t (&p)[NS]) {
-  if constexpr (NS == 2) {
-    const uint32_t h = bf16_bits(f);
-    p[0] = (uint16_t)h;
-    p[1] = (uint16_t)bf16_bits(f - __uint_as_float(h << 16));
-  } else {
-    // an infinity or NaN is its first plane alone (keeping a NaN a NaN)
-    const uint32_t u = __float_as_uint(f);
-    const bool special = (u & 0x7f800000u) == 0x7f800000u;
-    const float r1 = special ? 0.f : f - __uint_as_float(u & 0xffff0000u);
-    const uint32_t u1 = __float_as_uint(r1);
-    p[0] = (uint16_t)((u >> 16) | (special && (u & 0x007fffffu) ? 0x40u : 0u));
-    p[1] = (uint16_t)(u1 >> 16);
-    p[2] = (uint16_t)(__float_as_uint(r1 - __uint_as_float(u1 & 0xffff0000u)) >> 16);
-  }
+#pragma unroll
+  for (int i = 0; i < NS; ++i) p[i] = (uint16_t)(NS == 2 ? split2_plane(f, i) : split3_plane(f, i));
 }
 
 // Geometry of a block of TM output rows: its four waves, each wave's tiles
@@ -145,25 +126,26 @@ __global__ __launch_bounds__(kGrThreads, 2) void k_rows_gemm(RowsGemmArgs a) {
   }
   const int kl = ((lane & 3) ^ (((lane >> 2) >> 1) & 3)) * 8;  // this lane's k within a step (not W_down)
   // With more than two buffers every call issues its LOADS loads (out of
-  // range past the part's last step), so that a wait can count them.
+  // range past the part's last step), so that a wait can count them; out of
+  // range by addition, which leaves no branch.
   auto issue = [&](uint8_t* sw, uint8_t* sx, int st) {
     const int k0 = st * kGrK;
-    const bool on = G::BUFS == 2 || st < st1;
+    const uint32_t out = G::BUFS == 2 || st < st1 ? 0u : kOOB;
 #pragma unroll
     for (int q = 0; q < G::WQ; ++q) {
       const int i = G::WQ * w + q;
       if constexpr (MODE == kGrDown) {
         // rows past K lie past the matrix and read as zero
-        dma16(rw0, sw + i * 1024, on ? woff[q] + (uint32_t)k0 * row_bytes : kOOB);
+        dma16(rw0, sw + i * 1024, out + woff[q] + (uint32_t)k0 * row_bytes);
       } else {
-        dma16(is_up(i) ? rw1 : rw0, sw + i * 1024, on && k0 + kl < a.K ? woff[q] + (uint32_t)k0 * 2u : kOOB);
+        dma16(is_up(i) ? rw1 : rw0, sw + i * 1024, out + woff[q] + (uint32_t)k0 * 2u + (k0 + kl < a.K ? 0u : kOOB));
       }
     }
 #pragma unroll
     for (int p = 0; p < NS; ++p)
 #pragma unroll
       for (int q = 0; q < 2; ++q)
-        dma16(rx[p], sx + p * kGrN * 64 + (2 * w + q) * 1024, on ? xoff[q] + (uint32_t)k0 * 2u : kOOB);
+        dma16(rx[p], sx + p * kGrN * 64 + (2 * w + q) * 1024, out + xoff[q] + (uint32_t)k0 * 2u);
   };
 
   f32x4 acc[MI][NB];
@@ -216,39 +198,48 @@ __global__ __launch_bounds__(kGrThreads, 2) void k_rows_gemm(RowsGemmArgs a) {
     }
     __builtin_amdgcn_sched_group_barrier(0x008, 2 * NB * NS, 0);
   };
-  // A step: this wave's loads of it have landed (those of the BUFS - 2 steps
+  // A step: this wave's loads of it have landed (those of the LEFT steps
   // after it may be on their way) and its operand reads of the step before
   // are done; after the barrier that holds for every wave, so the loads of
   // step st + BUFS - 1 may overwrite the buffer of step st - 1.
-  constexpr int kBehind = G::LOADS * (G::BUFS - 2);
-  static_assert(kBehind < 64, "vmcnt is six bits");
-  auto step = [&](uint8_t* sw, uint8_t* sx, uint8_t* nw, uint8_t* nx, int st) {
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt((kBehind & 15) | ((kBehind >> 4) << 14) | 0x0070);  // vmcnt(kBehind) lgkmcnt(0)
+  auto step = [&](uint8_t* sw, uint8_t* sx, uint8_t* nw, uint8_t* nx, int st, auto left, auto more) {
+    wait_vm<decltype(left)::v * G::LOADS>();
+    wait_lds();
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    if (G::BUFS > 2 || st + 1 < st1) issue(nw, nx, st + G::BUFS - 1);
+    if (decltype(more)::v && (G::BUFS > 2 || st + 1 < st1)) issue(nw, nx, st + G::BUFS - 1);
+    __builtin_amdgcn_sched_barrier(0);  // the loads go out before the products
     multiply(sw, sx);
   };
-  issue(sw0, sx0, st0);
+  issue(sw0, sx0, st0);  // (a part has at least one step)
   if constexpr (G::BUFS > 2) issue(sw1, sx1, st0 + 1);
   if constexpr (G::BUFS > 3) issue(sw2, sx2, st0 + 2);
-  for (int st = st0; st < st1; st += G::BUFS) {
+  // whole rounds of the buffers in a loop without exits (with one after each
+  // step the compiler loses count of the loads at the loop's head and waits
+  // for all of them there), then the last steps
+  constexpr Const<G::BUFS - 2> left;
+  constexpr Const<1> more;
+  constexpr Const<0> last;
+  int st = st0;
+  for (; st + G::BUFS <= st1; st += G::BUFS) {
     if constexpr (G::BUFS == 2) {
-      step(sw0, sx0, sw1, sx1, st);
-      if (st + 1 < st1) step(sw1, sx1, sw0, sx0, st + 1);
+      step(sw0, sx0, sw1, sx1, st, left, more);
+      step(sw1, sx1, sw0, sx0, st + 1, left, more);
     } else if constexpr (G::BUFS == 3) {
-      step(sw0, sx0, sw2, sx2, st);
-      if (st + 1 < st1) step(sw1, sx1, sw0, sx0, st + 1);
-      if (st + 2 < st1) step(sw2, sx2, sw1, sx1, st + 2);
+      step(sw0, sx0, sw2, sx2, st, left, more);
+      step(sw1, sx1, sw0, sx0, st + 1, left, more);
+      step(sw2, sx2, sw1, sx1, st + 2, left, more);
     } else {
-      step(sw0, sx0, sw3, sx3, st);
-      if (st + 1 < st1) step(sw1, sx1, sw0, sx0, st + 1);
-      if (st + 2 < st1) step(sw2, sx2, sw1, sx1, st + 2);
-      if (st + 3 < st1) step(sw3, sx3, sw2, sx2, st + 3);
+      step(sw0, sx0, sw3, sx3, st, left, more);
+      step(sw1, sx1, sw0, sx0, st + 1, left, more);
+      step(sw2, sx2, sw1, sx1, st + 2, left, more);
+      step(sw3, sx3, sw2, sx2, st + 3, left, more);
     }
   }
-  __builtin_amdgcn_s_waitcnt(0x0070);  // no load is on its way to LDS when the block ends
+  if (st < st1) step(sw0, sx0, nullptr, nullptr, st, left, last);
+  if constexpr (G::BUFS > 2) { if (st + 1 < st1) step(sw1, sx1, nullptr, nullptr, st + 1, Const<G::BUFS - 3>(), last); }
+  if constexpr (G::BUFS > 3) { if (st + 2 < st1) step(sw2, sx2, nullptr, nullptr, st + 2, Const<G::BUFS - 4>(), last); }
+  wait_vm<0>();  // no load is on its way to LDS when the block ends
 
   // D[i][j] sits in lane j + 16 (i / 4), register i % 4: a lane holds four
   // consecutive output rows of one vector.

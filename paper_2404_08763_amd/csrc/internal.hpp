@@ -11,31 +11,17 @@
 
 namespace cats {
 
-// Batched path (bf16 weights, kBatchedMinRows..16 rows): gate and up on
-// the matrix cores, then the down-projection by column tiles.  Below 5 rows
-// the fused kernel is faster (one pass of its vector-ALU dot products over
-// the staged rows); from 5 rows its dot products cost more than the
-// matrix-core path, and above 8 it would need a second pass over the weights.
-#ifndef CATS_BATCHED_MIN_ROWS
-#define CATS_BATCHED_MIN_ROWS 5
-#endif
-constexpr int kBatchedMinRows = CATS_BATCHED_MIN_ROWS;
-constexpr int kBatchedWaves = 8;   // the down-projection kernel's waves per block
-// Waves of the gate/up kernel: each holds 1/16 of x's columns as matrix-core
-// operands, so at d = 4096 the operands and a tile of weights in flight fit
-// the 128 registers a wave has at four waves per SIMD.
-constexpr int kGateUpWaves = 16;
-constexpr int kDownCols = kBatchedWaves * 128;  // columns of a down-projection block
-constexpr int kDownRowChunk = 1024;             // rows a down block stages in LDS at once
+constexpr int kDownCols = 512;  // columns of a down-projection block
 
-struct BatchedArgs {
+struct GateUpArgs {
   const void* wg;      // [m x d] W_gate^T (bf16)
   const void* wu;      // [m x d] W_up^T
   const float* x;      // [B x d]
-  int B, d, m;
-  float t;
   int norm;            // RMSNorm x (unit gain) before the block
   float eps;           // its epsilon
+  int B, d, m;
+  float t;
+  int aux;             // write seg_v
   int* seg_j;          // [m] union-active neurons, per block from its first neuron
   uint32_t* seg_mask;  // [m] their row masks
   float* seg_v;        // [B x m] (aux only)
@@ -47,8 +33,8 @@ struct DownArgs {
   const void* wd;      // [m x d] W_down (bf16)
   float* partial;      // [NG x B x d]
   const int* seg_j;
+  const uint32_t* seg_mask;  // zero past a segment's entries
   const float* seg_h;
-  const int* seg_cnt;
   int B, d, m;
   int G;               // blocks of the gate/up kernel (segments)
   int NG;              // neuron groups (partials)
@@ -167,11 +153,12 @@ hipError_t launch_unfused_up(int wdtype_bf16, int nch, int bt, bool index, const
 hipError_t launch_unfused_down(int wdtype_bf16, int nch, int bt, bool index, const UnfusedArgs& a, int G,
                                hipStream_t s);
 
-// k-steps of the batched gate/up kernel for width d (0: no instantiation
-// covers d exactly; those widths use the fused kernel).
-int batched_ks(int d);
-hipError_t launch_gateup(bool dense, bool aux, const BatchedArgs& a, int G, hipStream_t s);
-hipError_t launch_down_mfma(const DownArgs& a, hipStream_t s);
+// The batched path (mlp_gateup.hip, mlp_down.hip): the bf16 planes x and h are
+// split into, and whether a call of B rows takes it.
+int batch_planes(int d, int B);
+bool batched_rows(int d, int m, int B);
+hipError_t launch_gateup(bool dense, int planes, const GateUpArgs& a, int G, hipStream_t s);
+hipError_t launch_down(int planes, const DownArgs& a, hipStream_t s);
 hipError_t launch_sparse_input(const SparseInputArgs& a, hipStream_t s);
 
 // Many-row products of the calibration (gemm_rows.hip): x as bf16 planes,

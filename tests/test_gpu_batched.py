@@ -1,0 +1,124 @@
+"""The matrix-core path for 5..16 rows at the edges of its tiles and splits,
+against 64-bit products in plain torch: neuron tiles of 1..8 per block and more
+than one round of them, 8- and 16-row operands, two and three planes of x,
+widths that end inside a 64-column step, lists, and RMSNorm in front."""
+import math
+
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+EPS = 1e-5
+TWO_PLANES = (512, 1024, 2048, 3072, 4096, 5120)
+SHAPES = [
+    (512, 7, 16),        # one-neuron blocks, two planes
+    (512, 5000, 8),      # two tiles
+    (1024, 700, 9),
+    (8192, 600, 8),      # one tile, the widest rows
+    (1032, 3000, 5),     # a width that ends inside a step
+    (2856, 7001, 11),
+    (136, 12000, 8),     # three tiles, fewer steps than waves
+    (136, 16000, 16),    # four tiles, 16-row operands
+    (200, 23000, 13),    # six tiles
+    (72, 33000, 6),      # more than eight tiles: a second round
+    (8, 65536, 5),       # the most neurons, the narrowest rows
+]
+
+
+def _P():
+    import paper_2404_08763_amd as P
+
+    return P
+
+
+def _silu(z):
+    return z / (1 + torch.exp(-z))
+
+
+def _inputs(d, m, B, seed):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    w = [(torch.randn((m, d), generator=g, device="cuda") * 0.05).bfloat16() for _ in range(3)]
+    return w, torch.randn((B, d), generator=g, device="cuda"), torch.randn((B, d), generator=g, device="cuda")
+
+
+def _gap(mag, k):
+    """A cutoff in the widest gap near the k-quantile: rounding decides no mask."""
+    s = mag.reshape(-1).sort().values
+    n = s.numel()
+    lo, hi = int(n * max(k - 0.02, 0)), min(int(n * (k + 0.02)) + 2, n - 1)
+    i = int(torch.argmax((s[lo + 1:hi + 1] - s[lo:hi]) / s[lo + 1:hi + 1])) + lo
+    return float(((s[i] + s[i + 1]) / 2).float())
+
+
+def _bound(d, B):
+    # two planes lose 2^-17 of each x and h (relative, random in sign); three
+    # lose nothing and the fp32 sums a few 2^-24 of the result
+    return 2.0 ** -15 if d in TWO_PLANES else 2.0 ** -18
+
+
+@pytest.mark.parametrize("d,m,B", SHAPES)
+def test_batched_shapes(d, m, B):
+    P = _P()
+    w, x, res = _inputs(d, m, B, d + m + B)
+    layer = P.Layer(*w)
+    ws = P.workspace(d, m, B)
+    g, u = (x.double() @ w[i].double().t() for i in range(2))
+    v = _silu(g)
+    for k in (0.5, 0.9):
+        t = _gap(v.abs(), k)
+        keep = v.abs() >= t
+        want = res.double() + torch.where(keep, v * u, torch.zeros_like(v)) @ w[2].double()
+        ws.random_(0, 256)  # the workspace may hold anything
+        y, aux = P.mlp_forward(layer, x, t, residual=res, ws=ws, aux=True)
+        assert torch.equal(y, P.mlp_forward(layer, x, t, residual=res, ws=ws))
+        assert ((y.double() - want).norm() / want.norm()).item() <= _bound(d, B)
+        for b in range(B):
+            idx = keep[b].nonzero()[:, 0]
+            n = int(aux["cnt"][b])
+            assert n == idx.numel() and torch.equal(aux["idx"][b, :n].long(), idx)
+            if n:
+                assert (aux["v"][b, :n].double() - v[b, idx]).norm() <= _bound(d, B) * v[b, idx].norm()
+                h = (v * u)[b, idx]
+                assert (aux["h"][b, :n].double() - h).norm() <= 2 * _bound(d, B) * h.norm()
+    want = res.double() + (v * u) @ w[2].double()
+    y = P.mlp_dense(layer, x, residual=res, ws=ws)
+    assert ((y.double() - want).norm() / want.norm()).item() <= _bound(d, B)
+    assert torch.equal(P.mlp_forward(layer, x, math.inf, residual=res, ws=ws), res)
+
+
+@pytest.mark.parametrize("d,m,B", [(4096, 300, 8), (2856, 3000, 7), (1032, 3000, 16)])
+def test_batched_rmsnorm(d, m, B):
+    P = _P()
+    w, x, _ = _inputs(d, m, B, 3)
+    x[B - 1] *= 1e-3  # a row whose own scale matters
+    xn = x.double() / torch.sqrt((x.double() ** 2).mean(dim=1, keepdim=True) + EPS)
+    g, u = (xn @ w[i].double().t() for i in range(2))
+    t = _gap(_silu(g).abs(), 0.5)
+    h = torch.where(_silu(g).abs() >= t, _silu(g) * u, torch.zeros_like(g))
+    want = h @ w[2].double()
+    y = P.stack_forward(P.Stack([P.Layer(*w)], [t]), x, eps=EPS).double() - x.double()
+    # (the stream's own rounding, 2^-24 of x, on top)
+    slack = 2.0 ** -23 * x.abs().max().item() * math.sqrt(d)
+    for b in range(B):
+        assert (y[b] - want[b]).norm() <= _bound(d, B) * want[b].norm() + slack
+
+
+def test_batched_special_values():
+    """Three planes: an infinity or NaN in one row spoils that row alone, as it
+    does in fp32 products, and large and tiny values lose nothing."""
+    P = _P()
+    d, m, B = 1032, 3000, 8
+    w, x, _ = _inputs(d, m, B, 11)
+    x[1, 7] = float("inf")
+    x[2, 9] = float("nan")
+    x[3] *= 1e30
+    x[4] *= 1e-30
+    y = P.mlp_dense(P.Layer(*w), x)
+    x64 = x.double()
+    want = (_silu(x64 @ w[0].double().t()) * (x64 @ w[1].double().t())) @ w[2].double()
+    assert not torch.isfinite(y[1]).any() and torch.isnan(y[2]).all()
+    for b in (0, 5, 6, 7):
+        assert (y[b].double() - want[b]).norm() <= _bound(d, B) * want[b].norm()
+    fine = want[3].abs() < 1e38
+    assert (torch.isfinite(y[3]) | ~fine).all()
