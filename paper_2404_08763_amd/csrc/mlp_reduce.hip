@@ -15,6 +15,14 @@ constexpr int kReduceThreads = 512;
 constexpr int kReduceWaves = kReduceThreads / kWaveSize;    // float4 columns per block
 constexpr int kReducePer = kFusedBlocks / kWaveSize;        // partials per lane
 static_assert(kFusedBlocks % kWaveSize == 0, "partials must split evenly over the lanes");
+// Up to kReduceFew partials (the batched path's neuron groups): a wave takes 16
+// consecutive float4 columns, its four rows of 16 lanes every fourth partial,
+// so each load covers four runs of 256 bytes; one column per wave would read
+// 16 bytes of each partial per lane and leave most lanes without one
+// (5120 columns, 25 partials, 16 rows: 4.0 us against 8.1).
+constexpr int kReduceFew = 64;
+constexpr int kReduceFewCols = kReduceThreads / 4;
+__host__ __device__ constexpr int reduce_cols(int G) { return G <= kReduceFew ? kReduceFewCols : kReduceWaves; }
 // List finalize: entries per thread per pass, and one count per wave and
 // entry slot, which one wave scans.
 constexpr int kFinPer = 8;
@@ -33,9 +41,38 @@ __global__ __launch_bounds__(kReduceThreads) void k_mlp_reduce(ReduceArgs a) {
   const int tid = threadIdx.x;
   const int lane = tid & (kWaveSize - 1);
   const int d4 = a.d >> 2;
-  const int ncb = (d4 + kReduceWaves - 1) / kReduceWaves;
+  const int ncb = (d4 + reduce_cols(a.G) - 1) / reduce_cols(a.G);
   const int nred = a.sum_y ? a.B * ncb : 0;
 
+  if ((int)blockIdx.x < nred && a.G <= kReduceFew) {
+    // y[b, c] = residual[b, c] + (s_0 + s_1) + (s_2 + s_3), s_r = the sum over k
+    // ascending of partial[4 k + r, b, c]
+    const int b = blockIdx.x / ncb, cb = blockIdx.x - b * ncb;
+    const int r = lane >> 4;
+    const int c4 = cb * kReduceFewCols + (tid / kWaveSize) * 16 + (lane & 15);
+    const __amdgpu_buffer_rsrc_t rp =
+        make_rsrc(a.partial, (uint32_t)((size_t)a.G * a.B * a.d * sizeof(float)));
+    u32x4 v[kReduceFew / 4];
+#pragma unroll
+    for (int k = 0; k < kReduceFew / 4; ++k) {
+      const int g = 4 * k + r;
+      v[k] = ld_buf16(rp, g < a.G && c4 < d4 ? (uint32_t)((((size_t)g * a.B + b) * a.d + (size_t)c4 * 4) * sizeof(float)) : kOOB);
+    }
+    f32x4 tot = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < kReduceFew / 4; ++k)
+      tot += f32x4{__uint_as_float(v[k].x), __uint_as_float(v[k].y), __uint_as_float(v[k].z), __uint_as_float(v[k].w)};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      tot[e] += __shfl_xor(tot[e], 16);
+      tot[e] += __shfl_xor(tot[e], 32);
+    }
+    if (r == 0 && c4 < d4) {
+      if (a.residual) tot = reinterpret_cast<const f32x4*>(a.residual + (size_t)b * a.d)[c4] + tot;
+      reinterpret_cast<f32x4*>(a.y + (size_t)b * a.d)[c4] = tot;
+    }
+    return;
+  }
   if ((int)blockIdx.x < nred) {
     // One wave per float4 column c of row b:
     //   y[b, c] = residual[b, c] + wave_sum over lanes of
@@ -190,7 +227,7 @@ __global__ __launch_bounds__(kReduceThreads) void k_mlp_reduce(ReduceArgs a) {
 
 hipError_t launch_reduce(const ReduceArgs& a, hipStream_t s) {
   const int d4 = a.d >> 2;
-  const int ncb = (d4 + kReduceWaves - 1) / kReduceWaves;
+  const int ncb = (d4 + reduce_cols(a.G) - 1) / reduce_cols(a.G);
   const int grid = (a.sum_y ? a.B * ncb : 0) + (a.aux ? a.B * fin_blocks(a.m) : 0);
   if (grid == 0) return hipSuccess;
   KernelTimer timer("k_mlp_reduce", s);
