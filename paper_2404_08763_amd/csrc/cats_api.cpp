@@ -860,20 +860,20 @@ size_t stack_calib_general(int d, int max_m, int N) {
   return cal > fwd ? cal : fwd;
 }
 
-// Workspace of the many-row propagation: the select scratch and general
-// region of the row-group path (activations, later the down-projection's
-// partial sums, which need one [N x d] at least), X, then the planes of
-// RMSNorm(X) and of h, and the select's histograms and results.
+// Workspace of the many-row propagation: the activations (later the
+// down-projection's partial sums, which need one [N x d] at least), X, then the
+// planes of RMSNorm(X) and of h, and the select's histograms and results.  A
+// workspace that holds the row groups' layout but not this one still works.
 struct StackCalibLayout {
-  size_t acts_bytes, X, xs, hs, hist, end;
+  size_t acts, acts_bytes, X, xs, hs, hist, end;
 };
 StackCalibLayout stack_calib_layout(int d, int max_m, int N, int L) {
   StackCalibLayout o;
   const size_t rows = round_up((size_t)N * d * sizeof(float), kAlign);
-  size_t general = stack_calib_general(d, max_m, N);
-  if (general < radix_bytes() + rows) general = radix_bytes() + rows;
-  o.acts_bytes = general - radix_bytes();
-  o.X = general;
+  const size_t acts = round_up((size_t)N * max_m * sizeof(float), kAlign);
+  o.acts = radix_bytes();
+  o.acts_bytes = acts > rows ? acts : rows;
+  o.X = o.acts + o.acts_bytes;
   o.xs = o.X + rows;
   o.hs = o.xs + planes_bytes(3, N, d);
   o.hist = o.hs + planes_bytes(3, N, max_m);
@@ -899,7 +899,7 @@ cats_status calibrate_stack_rows(const cats_layer* layers, int L, const float* c
                                  int ns, const StackCalibLayout& lay, void* ws, hipStream_t s, float* t_out) {
   char* w = static_cast<char*>(ws);
   const int d = layers[0].d;
-  float* acts = reinterpret_cast<float*>(w + radix_bytes());  // then the down-projection's partial sums
+  float* acts = reinterpret_cast<float*>(w + lay.acts);  // then the down-projection's partial sums
   float* X = reinterpret_cast<float*>(w + lay.X);
   uint16_t* hs = reinterpret_cast<uint16_t*>(w + lay.hs);
   uint32_t* hist = reinterpret_cast<uint32_t*>(w + lay.hist);
