@@ -1053,9 +1053,12 @@ cats_status cats_mlp_forward_topk(const cats_layer* layer, const float* x, int32
   st = check_ws(ws, ws_bytes, cats_topk_workspace_bytes(d, m, B));
   if (st != CATS_OK) return st;
   float* vbuf = reinterpret_cast<float*>(static_cast<char*>(ws) + base);
-  float* tbuf = reinterpret_cast<float*>(static_cast<char*>(ws) + base + round_up((size_t)B * m * sizeof(float), kAlign));
-  unsigned long long* ticket = reinterpret_cast<unsigned long long*>(
-      reinterpret_cast<char*>(tbuf) + round_up((size_t)B * sizeof(float), kAlign));
+  char* after_v = static_cast<char*>(ws) + base + round_up((size_t)B * m * sizeof(float), kAlign);
+  // the select writes the caller's cutoffs directly (a copy from the
+  // workspace afterwards was a fourth launch: 2 us of a one-row call)
+  float* tbuf = t_out ? t_out : reinterpret_cast<float*>(after_v);
+  unsigned long long* ticket =
+      reinterpret_cast<unsigned long long*>(after_v + round_up((size_t)B * sizeof(float), kAlign));
   const hipStream_t s = static_cast<hipStream_t>(stream);
   const int nch = cats::fused_nch(bf16, d);
   const int bt_max = cats::fused_bt_max(bf16, nch);
@@ -1099,10 +1102,6 @@ cats_status cats_mlp_forward_topk(const cats_layer* layer, const float* x, int32
   }
   st = run_mlp(layer, x, B, 0.f, false, residual, y, aux, ws, base, stream, false, 0.f, vbuf, tbuf);
   if (st != CATS_OK) return st;
-  if (t_out) {
-    e = hipMemcpyAsync(t_out, tbuf, (size_t)B * sizeof(float), hipMemcpyDeviceToDevice, s);
-    if (e != hipSuccess) return hip_fail(e, "cutoff copy");
-  }
   return sync_check(stream, "cats_mlp_forward_topk");
 }
 
