@@ -120,12 +120,15 @@ def _check(status: int) -> None:
         raise CatsError(status, msg)
 
 
-def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+def _stream() -> int:
+    """The current stream of the current device, as torch keeps it: the handle
+    itself, without a Stream object around it (2.9 us of a call's 11)."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
-def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
+    # (an address or None, which the void* parameters take as they are)
+    return None if t is None else t.data_ptr()
 
 
 def _dev(t: torch.Tensor, name: str, dtype=None):
@@ -160,6 +163,7 @@ class Layer:
                 raise ValueError(f"{n} has shape {tuple(w.shape)}, expected {(m, d)}")
         self._c = _Layer(d, m, _wdtype(self.w_gate_t.dtype), self.w_gate_t.data_ptr(),
                          self.w_up_t.data_ptr(), self.w_down.data_ptr())
+        self._ref = ctypes.byref(self._c)
 
     @property
     def d(self) -> int:
@@ -171,7 +175,7 @@ class Layer:
 
     @property
     def c(self):
-        return ctypes.byref(self._c)
+        return self._ref
 
 
 def version() -> int:
@@ -250,11 +254,12 @@ def _rows_of(x: torch.Tensor, d: int, name: str = "x") -> int:
     """Rows of a [B, d] (or [d]) activation tensor; raises before any call
     into the library when its width is not the layer's d, since the kernels
     read and write B * d floats through raw pointers."""
-    if x.dim() not in (1, 2):
-        raise ValueError(f"{name} must be [d] or [B, d], got shape {tuple(x.shape)}")
-    if int(x.shape[-1]) != d:
-        raise ValueError(f"{name} has width {int(x.shape[-1])}, the layer has d={d}")
-    return _rows(x)
+    shape = x.shape
+    if len(shape) not in (1, 2):
+        raise ValueError(f"{name} must be [d] or [B, d], got shape {tuple(shape)}")
+    if shape[-1] != d:
+        raise ValueError(f"{name} has width {int(shape[-1])}, the layer has d={d}")
+    return 1 if len(shape) == 1 else shape[0]
 
 
 def _numel_is(t: Optional[torch.Tensor], n: int, name: str) -> None:
