@@ -176,8 +176,9 @@ __device__ __forceinline__ void wait_lds() {
 }
 
 // 16 bytes per lane from memory to LDS (lane l's at dst + 16 l).
+template <int POLICY = 0>
 __device__ __forceinline__ void dma16(__amdgpu_buffer_rsrc_t r, uint8_t* dst, uint32_t off) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)dst, 16, (int)off, 0, 0, 0);
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)dst, 16, (int)off, 0, 0, POLICY);
 }
 
 // SiLU(z) = z / (1 + e^{-z}).  For z below about -88 e^{-z} overflows to

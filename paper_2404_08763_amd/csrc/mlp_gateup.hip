@@ -6,10 +6,10 @@
 // W_up rows are read for the union of the rows' active neurons only (Eq. 1,
 // 2 and 5 with one mask per row).
 //
-// Measured (this kernel, us): 4096 x 11008 dense 36 at 8 and 16 rows (5.0 TB/s;
-// the kernel that kept x in registers, one sixteenth of the columns per wave,
-// 40 and 43), k = 0.9 at 16 rows 34 (41); 5120 x 13824 at 16 rows 56 (63);
-// 8192 x 28672 dense at 8 rows 160 (5.9 TB/s; the fused kernel in two passes
+// Measured (this kernel, us): 4096 x 11008 dense at 16 rows 32.4 (5.6 TB/s; the
+// kernel that kept x in registers, one sixteenth of the columns per wave, 43),
+// k = 0.7 at 8 / 16 rows 33 / 35 (40 / 44); 5120 x 13824 at 16 rows 53 (63);
+// 8192 x 28672 dense at 8 rows 144 (6.5 TB/s; the fused kernel in two passes
 // 2 x 283); 2856 x 7001 at 11 rows 22 (2 x 40).
 //
 // What bounds it: reading the weights (2 or 3 products per weight and row
@@ -76,7 +76,8 @@ struct GuGeom {
   static_assert(BUFS >= 2 && (BUFS - 1) * OPS < 64, "two steps must fit, and vmcnt is six bits");
 };
 
-template <int T, int NS, int XR, bool DENSE>
+// STREAM: the weights are read with the non-temporal policy.
+template <int T, int NS, int XR, bool DENSE, bool STREAM>
 __global__ __launch_bounds__((GuGeom<T, NS, XR>::THREADS)) void k_mlp_gateup(GateUpArgs a) {
   typedef GuGeom<T, NS, XR> G;
   constexpr int W = G::W;
@@ -153,7 +154,7 @@ __global__ __launch_bounds__((GuGeom<T, NS, XR>::THREADS)) void k_mlp_gateup(Gat
       for (int t = 0; t < T; ++t)
 #pragma unroll
         for (int i = 0; i < 2; ++i)
-          dma16(up(t) ? ru : rg, s + w * G::WB + t * 2048 + i * 1024, rb[2 * t + i] + off);
+          dma16<STREAM ? 2 /* nt */ : 0>(up(t) ? ru : rg, s + w * G::WB + t * 2048 + i * 1024, rb[2 * t + i] + off);
 #pragma unroll
       for (int i = 0; i < G::XI; ++i)
         dma16(rx, s + w * G::WB + T * 2048 + i * 1024,
@@ -437,14 +438,25 @@ static hipError_t launch_gateup_t(int planes, const GateUpArgs& a, int G, hipStr
   const dim3 grid(G), block(GuGeom<T, 2, 8>::THREADS);
   // (eight tiles and 16 rows of x leave no room for a second step)
   constexpr int T16 = T > 6 ? 6 : T;
-#define CATS_GU(TT, NS, XR) \
-  hipExtLaunchKernelGGL((k_mlp_gateup<TT, NS, XR, DENSE>), grid, block, 0, s, timer.start(), timer.stop(), 0, a)
+#define CATS_GU(TT, NS, XR, STREAM) \
+  hipExtLaunchKernelGGL((k_mlp_gateup<TT, NS, XR, DENSE, STREAM>), grid, block, 0, s, timer.start(), timer.stop(), 0, a)
+  // Non-temporal reads for rows of whole lines in blocks that the 256 MB
+  // last-level cache cannot hold two of.  From memory they are 5 to 10%
+  // faster (4096 x 11008 dense at 16 rows 37.0 us cached, 32.4 so; 24 blocks of
+  // 2048 x 5632 in turn 29.7 / 28.3 a call), from that cache 7% slower (three
+  // such blocks in turn 25.5 / 27.9); where lines straddle rows and steps they
+  // fetch them twice (2856 x 7001 at 11 rows 22.2 / 28.1).
+  const bool stream = a.d % 64 == 0 && (uint64_t)a.m * a.d * 6 >= (144ull << 20);
   if (a.B <= 8) {
-    if (planes == 2) CATS_GU(T, 2, 8);
-    else CATS_GU(T, 3, 8);
+    if (planes == 2 && stream) CATS_GU(T, 2, 8, true);
+    else if (planes == 2) CATS_GU(T, 2, 8, false);
+    else if (stream) CATS_GU(T, 3, 8, true);
+    else CATS_GU(T, 3, 8, false);
   } else {
-    if (planes == 2) CATS_GU(T16, 2, 16);
-    else CATS_GU(T16, 3, 16);
+    if (planes == 2 && stream) CATS_GU(T16, 2, 16, true);
+    else if (planes == 2) CATS_GU(T16, 2, 16, false);
+    else if (stream) CATS_GU(T16, 3, 16, true);
+    else CATS_GU(T16, 3, 16, false);
   }
 #undef CATS_GU
   return hipGetLastError();
