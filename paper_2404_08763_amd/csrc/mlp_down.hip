@@ -20,8 +20,8 @@
 //  - h enters as NS bf16 planes (as x does in the gate/up kernel; products
 //    exact, fp32 accumulation), staged per block as [plane][row][list entry].
 // Measured (us, before: 1024-column blocks, three round trips): 4096 x 11008 at
-// 8 / 16 rows 19.1 / 21.0 (20.5 / 22.6), 5120 x 13824 at 16 rows 30.0 (33.9),
-// 8192 x 28672 at 8 rows 77 (80; 6.1 TB/s), 512 x 1408 at 8 rows 6.3 (8.3).
+// 8 / 16 rows 18.6 / 20.2 (20.5 / 22.6), 5120 x 13824 at 16 rows 29.2 (33.9),
+// 8192 x 28672 at 8 rows 76 (80; 6.2 TB/s), 512 x 1408 at 8 rows 6.3 (8.3).
 #include "device.hpp"
 #include "internal.hpp"
 
@@ -168,19 +168,26 @@ __global__ __launch_bounds__(kDnThreads) void k_mlp_down(DownArgs a) {
         for (int p = 1; p < NS; ++p) accl[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv[p], accl[t], 0, 0, 0);
       }
     };
+    // Whole pairs of this half's steps in a loop without a way round either of
+    // them, and the next chunk's entries asked for whether there are any or
+    // not: with a condition the compiler cannot count the loads in flight and
+    // waits for all of them at the loop's head.
     u32x4 rA[8], rB[8];
     load_step(rA, wr);
     load_step(rB, wr + 2);
-    if (c0 + kDnChunk < p1) fetch(c0 + kDnChunk);  // the next chunk's entries meanwhile
-    for (int st = wr; st < nsteps; st += 4) {
+    fetch(c0 + kDnChunk);
+    int st = wr;
+    for (; st + 2 < nsteps; st += 4) {
       write_step(rA);
       load_step(rA, st + 4);
       compute_step(st);
-      if (st + 2 < nsteps) {
-        write_step(rB);
-        load_step(rB, st + 6);
-        compute_step(st + 2);
-      }
+      write_step(rB);
+      load_step(rB, st + 6);
+      compute_step(st + 2);
+    }
+    if (st < nsteps) {
+      write_step(rA);
+      compute_step(st);
     }
   }
 
