@@ -477,18 +477,29 @@ static bool two_plane_width(int d) {
 int batch_planes(int d, int B) { return B >= 5 && two_plane_width(d) ? 2 : 3; }
 
 // Whether the matrix-core path (three launches) takes a call, or the fused
-// kernel (two, its products on the vector ALUs).  Up to 4 rows the fused
-// kernel's dot products keep up with the weights (4096 x 11008, k = 0.7, 4
-// rows: 54 us against 58); from 9 rows it reads the weights twice.  In between
-// it is faster only for small narrow blocks, where a launch weighs more than
-// the products (us, fused / matrix cores: 512 x 1408 at 5 rows 12.5 / 15.3, at 8
+// kernel (two, its products on the vector ALUs).
+// One and two rows: the fused kernel, whose dot products keep up with the
+// weights (2 rows, us, fused / matrix cores: 4096 x 11008 40 / 45).
+// Three and four rows: it keeps up while x's rows leave it two waves per SIMD,
+// up to d = 5120 (3 rows at 4096 x 11008: 49.0 / 50.3); above that the matrix
+// cores are faster but for the smallest blocks (8192 x 28672 at k = 0.5, 3 rows
+// 251 / 208, 4 rows 296 / 222; 6144 x 2000, 3 rows 41 / 32; 5640 x 600, 3 rows
+// 30.0 / 29.1; 8192 x 512, 3 rows 31.6 / 33.2, 4 rows 37.7 / 33.4).  Four rows
+// of whole 128-byte lines of weights also where reading them outweighs the
+// third launch (5120 x 13824 88 / 82; 4096 x 11008 54.0 / 52.1; 4096 x 6200
+// 41.2 / 38.8; 1024 x 28000 58 / 45; rows that end inside a line are read
+// better by the fused kernel: 2856 x 20000 78 / 86).
+// From 5 rows the fused kernel is faster only for small narrow blocks, where a
+// launch weighs more than the products (512 x 1408 at 5 rows 12.5 / 15.3, at 8
 // rows 14.6 / 15.3; 1024 x 1024 at 5 rows 15.0 / 17.4; 512 x 3000 at 5 rows
 // 15.4 / 15.8, at 8 rows 18.2 / 16.0; 1024 x 2048 at 6 rows 17.4 / 16.6;
 // 1000 x 3000 at 5 rows 19.2 / 18.0).  At the three-plane widths small blocks
 // keep the fused kernel at every row count: there the forward is bit for bit
 // the separate kernels' result (cats_mlp_forward_unfused).
 bool batched_rows(int d, int m, int B) {
-  if (B < 5) return false;
+  const int64_t md = (int64_t)m * d;
+  if (B < 3) return false;
+  if (B < 5) return d > 5120 ? B * md >= 10000000 : B == 4 && d % 64 == 0 && md >= 25000000;
   if ((int64_t)B * m * (d < 512 ? 512 : d) > 8000000) return true;
   return two_plane_width(d) && (B > 8 || d > 1024);
 }
