@@ -138,49 +138,6 @@ __device__ __forceinline__ uint32_t bf16_bits(float f) {
   return ((u & 0x7fffffffu) > 0x7f800000u) ? ((u >> 16) | 0x40u) : rne;
 }
 
-// Plane p of a value as two bf16 planes: the nearest hi, the nearest lo.
-__device__ __forceinline__ uint32_t split2_plane(float f, int p) {
-  const uint32_t h = bf16_bits(f);
-  return p == 0 ? h : bf16_bits(f - __uint_as_float(h << 16));
-}
-
-// Plane p of a value as three bf16 planes of 8 significand bits each, cut (not
-// rounded), whose sum is the value.  An infinity or NaN is its first plane
-// alone, so products make of it what fp32 products do.
-__device__ __forceinline__ uint32_t split3_plane(float f, int p) {
-  const uint32_t u = __float_as_uint(f);
-  const bool special = (u & 0x7f800000u) == 0x7f800000u;
-  const float r1 = special ? 0.f : f - __uint_as_float(u & 0xffff0000u);
-  const uint32_t u1 = __float_as_uint(r1);
-  if (p == 0) return (u >> 16) | (special && (u & 0x007fffffu) ? 0x40u : 0u);
-  if (p == 1) return u1 >> 16;
-  return __float_as_uint(r1 - __uint_as_float(u1 & 0xffff0000u)) >> 16;
-}
-
-// A number known to the compiler, as an argument.
-template <int V> struct Const { static constexpr int v = V; };
-
-// Wait until at most N of this wave's memory operations are outstanding
-// (they complete in order); no other counter is waited for.
-template <int N> __device__ __forceinline__ void wait_vm() {
-  static_assert(N >= 0 && N < 64, "vmcnt is six bits");
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0f70);
-  asm volatile("" ::: "memory");
-}
-// Wait until this wave's LDS reads and writes are done.
-__device__ __forceinline__ void wait_lds() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt(0xc07f);
-  asm volatile("" ::: "memory");
-}
-
-// 16 bytes per lane from memory to LDS (lane l's at dst + 16 l).
-template <int POLICY = 0>
-__device__ __forceinline__ void dma16(__amdgpu_buffer_rsrc_t r, uint8_t* dst, uint32_t off) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)dst, 16, (int)off, 0, 0, POLICY);
-}
-
 // SiLU(z) = z / (1 + e^{-z}).  For z below about -88 e^{-z} overflows to
 // +inf and the result is -0, whose magnitude 0 is masked by any t > 0.
 __device__ __forceinline__ float silu(float z) { return z / (1.0f + __expf(-z)); }

@@ -21,7 +21,7 @@
 // 1.46 (the 256 x 128 tiles that split x per block: 618 us).  The order of LDS
 // reads and products, wave priority and 512 blocks against 688 tiles were
 // within 2%.
-#include "device.hpp"
+#include "stream.hpp"
 #include "internal.hpp"
 
 namespace cats {

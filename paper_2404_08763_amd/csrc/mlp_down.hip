@@ -22,7 +22,7 @@
 // Measured (us, before: 1024-column blocks, three round trips): 4096 x 11008 at
 // 8 / 16 rows 18.6 / 20.2 (20.5 / 22.6), 5120 x 13824 at 16 rows 29.2 (33.9),
 // 8192 x 28672 at 8 rows 76 (80; 6.2 TB/s), 512 x 1408 at 8 rows 6.3 (8.3).
-#include "device.hpp"
+#include "stream.hpp"
 #include "internal.hpp"
 
 namespace cats {

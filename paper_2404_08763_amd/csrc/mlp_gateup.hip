@@ -33,7 +33,7 @@
 //  - A block owns the fused kernel's neuron range: gate tiles first, then
 //    the block's active neurons, listed in order, as up tiles; DENSE takes a
 //    neuron's gate and up tile in the same step (x is then read once).
-#include "device.hpp"
+#include "stream.hpp"
 #include "internal.hpp"
 
 namespace cats {
