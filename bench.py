@@ -609,10 +609,11 @@ def profile_set(P, W, torch, layers, xs, thr, ks, calls=6):
         xb = [xs[(c * B) % ntok : (c * B) % ntok + B].contiguous() for c in range(calls)]
         for k in ((k5,) if B > 1 else ks):
             U = union(B, thr[k])
-            kern = ["k_mlp_fused", "k_mlp_reduce"] if B <= 4 else ["k_mlp_gateup_mfma", "k_mlp_down_mfma", "k_mlp_reduce"]
+            kern = ["k_mlp_fused", "k_mlp_reduce"] if B < 4 else ["k_mlp_gateup", "k_mlp_down", "k_mlp_reduce"]
             run(f"forward B={B} k={k}", kern, lambda c, k=k: P.mlp_forward(layers[c % R], xb[c], thr[k], out=y, ws=ws),
                 sw * d * (m + 2 * U) + 8 * B * d)
-        run(f"dense B={B}", ["k_mlp_fused (dense)" if B <= 4 else "k_mlp_gateup_mfma (dense)", "k_mlp_reduce"],
+        run(f"dense B={B}",
+            ["k_mlp_fused (dense)", "k_mlp_reduce"] if B < 4 else ["k_mlp_gateup (dense)", "k_mlp_down", "k_mlp_reduce"],
             lambda c: P.mlp_dense(layers[c % R], xb[c], out=y, ws=ws), 3 * sw * d * m + 8 * B * d)
         del ws
     x1 = [xs[c % ntok : c % ntok + 1].contiguous() for c in range(calls)]
@@ -628,8 +629,7 @@ def profile_set(P, W, torch, layers, xs, thr, ks, calls=6):
         run(f"unfused {mode} B=1 k={k5}", ["k_gate_v", "k_unfused_up", "k_unfused_down", "k_mlp_reduce"],
             lambda c, mode=mode: P.mlp_forward_unfused(layers[c % R], x1[c], t5, mode=mode, out=y1),
             sw * d * (m + 2 * U1) + 8 * d + 16 * m)
-    # the Llama2-13B-shaped block at 16 rows: the matrix-core path at
-    # d = 5120 (ten k-steps per wave)
+    # the Llama2-13B-shaped block at 16 rows: the matrix-core path at d = 5120
     c4 = W.CONFIGS["C4"]
     g4, u4, d4 = W.weights(c4.d, c4.m, c4.wdtype)
     l4 = P.layer_from_math(g4.to(dev), u4.to(dev), d4.to(dev))
@@ -645,10 +645,10 @@ def profile_set(P, W, torch, layers, xs, thr, ks, calls=6):
         _, a4 = P.mlp_forward(l4, xb4[c], t4, aux=True, ws=ws4)
         cnt, idx = a4["cnt"].cpu().numpy(), a4["idx"].cpu().numpy()
         U4.append(len(np.unique(np.concatenate([idx[b, : cnt[b]] for b in range(16)]))))
-    run(f"13B-shaped forward B=16 k={k5}", ["k_mlp_gateup_mfma", "k_mlp_down_mfma", "k_mlp_reduce"],
+    run(f"13B-shaped forward B=16 k={k5}", ["k_mlp_gateup", "k_mlp_down", "k_mlp_reduce"],
         lambda c: P.mlp_forward(l4s[c % 2], xb4[c], t4, out=y4, ws=ws4),
         sw * c4.d * (c4.m + 2 * float(np.mean(U4))) + 8 * 16 * c4.d)
-    run("13B-shaped dense B=16", ["k_mlp_gateup_mfma (dense)", "k_mlp_down_mfma", "k_mlp_reduce"],
+    run("13B-shaped dense B=16", ["k_mlp_gateup (dense)", "k_mlp_down", "k_mlp_reduce"],
         lambda c: P.mlp_dense(l4s[c % 2], xb4[c], out=y4, ws=ws4), 3 * sw * c4.d * c4.m + 8 * 16 * c4.d)
     del l4s, l4, ws4
     qc = W.CONFIGS["QKV"]

@@ -1,4 +1,4 @@
-// Down-projection of a batch (5..16 rows, bf16 weights) on the matrix cores:
+// Down-projection of a batch (3..16 rows, bf16 weights) on the matrix cores:
 //   partial_q[b][c] = sum over the union-active neurons j of group q of
 //                     h[b][j] W_down[j][c]
 // from the segment lists of k_mlp_gateup; k_mlp_reduce sums the groups in order.

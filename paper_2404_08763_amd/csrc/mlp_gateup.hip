@@ -1,4 +1,4 @@
-// Gate and up projections of a batch (5..16 rows, bf16 weights, any width) on
+// Gate and up projections of a batch (3..16 rows, bf16 weights, any width) on
 // the matrix cores.
 //
 //   v_bj = SiLU(x_b . W_gate[:, j]);  (b, j) active when |v_bj| >= t
