@@ -58,6 +58,11 @@ __global__ __launch_bounds__(kReduceThreads) void k_mlp_reduce(ReduceArgs a) {
       const int g = 4 * k + r;
       v[k] = ld_buf16(rp, g < a.G && c4 < d4 ? (uint32_t)((((size_t)g * a.B + b) * a.d + (size_t)c4 * 4) * sizeof(float)) : kOOB);
     }
+    u32x4 rv = {0u, 0u, 0u, 0u};
+    if (a.residual) {  // with the partials' loads, not a round trip after them
+      const __amdgpu_buffer_rsrc_t rr = make_rsrc(a.residual + (size_t)b * a.d, (uint32_t)(a.d * sizeof(float)));
+      rv = ld_buf16(rr, r == 0 && c4 < d4 ? (uint32_t)c4 * 16u : kOOB);
+    }
     f32x4 tot = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int k = 0; k < kReduceFew / 4; ++k)
@@ -68,7 +73,8 @@ __global__ __launch_bounds__(kReduceThreads) void k_mlp_reduce(ReduceArgs a) {
       tot[e] += __shfl_xor(tot[e], 32);
     }
     if (r == 0 && c4 < d4) {
-      if (a.residual) tot = reinterpret_cast<const f32x4*>(a.residual + (size_t)b * a.d)[c4] + tot;
+      if (a.residual)
+        tot = f32x4{__uint_as_float(rv.x), __uint_as_float(rv.y), __uint_as_float(rv.z), __uint_as_float(rv.w)} + tot;
       reinterpret_cast<f32x4*>(a.y + (size_t)b * a.d)[c4] = tot;
     }
     return;
