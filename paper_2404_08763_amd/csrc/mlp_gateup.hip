@@ -296,7 +296,10 @@ __global__ __launch_bounds__((GuGeom<T, NS, XR>::THREADS)) void k_mlp_gateup(Gat
     __syncthreads();                     // nor any other wave's
     f32x4* red = reinterpret_cast<f32x4*>(s0);
 #pragma unroll
-    for (int t = 0; t < T; ++t) red[(w * T + t) * kWaveSize + lane] = (acc[t][0] + acc[t][1]) + acl[t];
+    for (int t = 0; t < T; ++t) {
+      const f32x4 first = acc[t][0] + acc[t][1];
+      red[(w * T + t) * kWaveSize + lane] = NS == 3 ? add_lower_planes(first, acl[t]) : first + acl[t];
+    }
     if (sq) {
       // the four lanes of a row, then the waves, in a fixed order
       float q = ss + __shfl_xor(ss, 16);
@@ -317,12 +320,15 @@ __global__ __launch_bounds__((GuGeom<T, NS, XR>::THREADS)) void k_mlp_gateup(Gat
   // columns that hold row b's planes in plane order.
   auto dot = [&](int t, int i, int b) -> float {
     const float* red = reinterpret_cast<const float*>(s0);
-    float sum = 0.f;
+    float sum = 0.f, first = 0.f;
 #pragma unroll
-    for (int p = 0; p < G::COLS; ++p)
+    for (int p = 0; p < G::COLS; ++p) {
 #pragma unroll
       for (int k = 0; k < W; ++k)
         sum += red[((k * T + t) * kWaveSize + p * XR + b + 16 * (i >> 2)) * 4 + (i & 3)];
+      if (p == 0) first = sum;
+    }
+    if (NS == 3 && !is_finite(first)) sum = first;  // as in add_lower_planes
     return a.norm ? sum * l_scale[b] : sum;
   };
 

@@ -25,6 +25,21 @@ __device__ __forceinline__ uint32_t split3_plane(float f, int p) {
   return __float_as_uint(r1 - __uint_as_float(u1 & 0xffff0000u)) >> 16;
 }
 
+__device__ __forceinline__ bool is_finite(float f) {
+  return (__float_as_uint(f) & 0x7f800000u) != 0x7f800000u;
+}
+// Sums of three-plane products: the first plane's, to which the other two's
+// are added where it is finite.  An infinite weight makes of the first plane
+// (which has the value's sign, and is zero only where the value is zero or
+// below 2^-126) what it makes of the value itself, but a NaN of a lower plane
+// that is zero.
+__device__ __forceinline__ f32x4 add_lower_planes(f32x4 first, f32x4 lower) {
+  f32x4 r;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) r[e] = is_finite(first[e]) ? first[e] + lower[e] : first[e];
+  return r;
+}
+
 // A number known to the compiler, as an argument.
 template <int V> struct Const { static constexpr int v = V; };
 

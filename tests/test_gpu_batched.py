@@ -130,3 +130,31 @@ def test_batched_special_values(d, m, B):
         assert (y[b].double() - want[b]).norm() <= _bound(d, B) * want[b].norm()
     fine = want[3].abs() < 1e38
     assert (torch.isfinite(y[3]) | ~fine).all()
+
+
+@pytest.mark.parametrize("d,m,B", [(1032, 3000, 8), (1032, 3000, 16), (5128, 700, 4)])
+def test_batched_infinite_weights(d, m, B):
+    """Three planes: an infinite weight makes of a result what it makes of it in
+    fp32 products (its other planes are zero for many x and h, and 0 x inf is
+    NaN): one in W_down leaves all other columns alone, one in W_up makes every
+    column infinite, one in W_gate every column of the rows it turns positive."""
+    P = _P()
+    w, x, _ = _inputs(d, m, B, 17)
+    x = torch.where(x.abs() < 0.1, torch.ones_like(x), x)  # no zeros; 1 has only its first plane
+    x[:, 3] = torch.where(torch.arange(B, device="cuda") % 2 == 0, 1.0, -1.0)
+    for which, j, c, sign in ((2, 5, 11, 1.0), (2, m - 1, d - 1, -1.0), (1, 5, 3, -1.0), (0, 5, 3, 1.0)):
+        wi = [v.clone() for v in w]
+        wi[which][j, c] = sign * math.inf
+        wi[2][j] = torch.where(wi[2][j] == 0, torch.ones_like(wi[2][j]), wi[2][j])
+        x64 = x.double()
+        h = _silu(x64 @ wi[0].double().t()) * (x64 @ wi[1].double().t())
+        want = h @ wi[2].double()
+        inf = torch.isinf(want)
+        assert inf.any() and (which == 0 or not torch.isnan(want).any())
+        for y in (P.mlp_dense(P.Layer(*wi), x), P.mlp_forward(P.Layer(*wi), x, 0.0)):
+            assert torch.equal(torch.isnan(y), torch.isnan(want))
+            assert torch.equal(y[inf].double(), want[inf])
+            for b in range(B):
+                ok = torch.isfinite(want[b])
+                if ok.any():
+                    assert (y[b, ok].double() - want[b, ok]).norm() <= _bound(d, B) * want[b, ok].norm()

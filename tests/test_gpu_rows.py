@@ -113,3 +113,24 @@ def test_wide_select_exact(n, shift):
         assert P.threshold_from_acts(a, k, ws=torch.empty(1280, dtype=torch.uint8, device="cuda")) == want
     same = torch.full((n,), 0.25, device="cuda")
     assert P.threshold_from_acts(same, 0.5) == 0.25
+
+
+def test_calibrate_stack_rows_infinite_weight():
+    """Three planes: an infinite weight in the second layer leaves the first
+    two cutoffs as they are (its neuron's few activations lie above them), and
+    everything behind it is NaN, as with the 16-row groups."""
+    P = _P()
+    d, m, N = 1032, 693, 35
+    for which in range(3):
+        w = _layers(d, m, 4, 21)
+        x = torch.randn((N, d), generator=torch.Generator(device="cuda").manual_seed(22), device="cuda")
+        plain = P.calibrate_stack(P.Stack([P.Layer(*v) for v in w]), x, 0.5, eps=EPS)
+        w[1][which][5, 7] = math.inf
+        stack = P.Stack([P.Layer(*v) for v in w])
+        groups = max(1280 + (N * m * 4 + 255) // 256 * 256, P.workspace_bytes(d, m, 16)) + 2 * ((N * d * 4 + 255) // 256 * 256)
+        ws = torch.empty(groups, dtype=torch.uint8, device="cuda")
+        for t in (P.calibrate_stack(stack, x, 0.5, eps=EPS), P.calibrate_stack(stack, x, 0.5, eps=EPS, ws=ws)):
+            assert t[0] == pytest.approx(plain[0], rel=1e-5)
+            # (one neuron of 693 moves the middle rank by at most N places)
+            assert t[1] == pytest.approx(plain[1], rel=1e-2)
+            assert all(math.isnan(v) for v in t[2:])
