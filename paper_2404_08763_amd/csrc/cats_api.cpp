@@ -179,12 +179,14 @@ int batch_tile(int rows) {
   return bt;
 }
 
-// Shared body of forward and dense.
-// norm: x is RMSNorm'ed (unit gain, eps) inside the fused kernel first.
+// Shared body of forward, dense and top-k.
+// norm: x is RMSNorm'ed (unit gain, eps) inside the block's first kernel.
+// vin, vin_t: top-k's gate activations and cutoffs; t_out receives the latter
+// with the last launch.
 cats_status run_mlp(const cats_layer* L, const float* x, int32_t B, float t, bool dense,
                     const float* residual, float* y, const cats_forward_aux* aux, void* ws,
                     size_t ws_bytes, void* stream, bool norm = false, float eps = 0.f,
-                    const float* vin = nullptr, const float* vin_t = nullptr) {
+                    const float* vin = nullptr, const float* vin_t = nullptr, float* t_out = nullptr) {
   cats_status st = check_layer(L);
   if (st != CATS_OK) return st;
   if (!x || !y) return fail(CATS_ERR_NULL, "x or y is NULL");
@@ -328,6 +330,11 @@ cats_status run_mlp(const cats_layer* L, const float* x, int32_t B, float t, boo
     ra.active_cnt = (want_aux && aux->active_cnt) ? aux->active_cnt + b0 : nullptr;
     ra.active_v = (want_aux && aux->active_v) ? aux->active_v + (size_t)b0 * m : nullptr;
     ra.active_h = (want_aux && aux->active_h) ? aux->active_h + (size_t)b0 * m : nullptr;
+    if (t_out && b0 + bp == B) {
+      ra.t_src = vin_t;
+      ra.t_dst = t_out;
+      ra.t_n = B;
+    }
     e = cats::launch_reduce(ra, s);
     if (e != hipSuccess) return hip_fail(e, "reduce launch");
   }
@@ -1064,12 +1071,12 @@ cats_status cats_mlp_forward_topk(const cats_layer* layer, const float* x, int32
   st = check_ws(ws, ws_bytes, cats_topk_workspace_bytes(d, m, B));
   if (st != CATS_OK) return st;
   float* vbuf = reinterpret_cast<float*>(static_cast<char*>(ws) + base);
-  char* after_v = static_cast<char*>(ws) + base + round_up((size_t)B * m * sizeof(float), kAlign);
-  // the select writes the caller's cutoffs directly (a copy from the
-  // workspace afterwards was a fourth launch: 2 us of a one-row call)
-  float* tbuf = t_out ? t_out : reinterpret_cast<float*>(after_v);
-  unsigned long long* ticket =
-      reinterpret_cast<unsigned long long*>(after_v + round_up((size_t)B * sizeof(float), kAlign));
+  // The cutoffs that the kernels use stay in the workspace: the caller's array
+  // may be shared with calls on other streams.  The last launch copies them
+  // out (a copy of its own was a fourth launch: 2 us of a one-row call).
+  float* tbuf = reinterpret_cast<float*>(static_cast<char*>(ws) + base + round_up((size_t)B * m * sizeof(float), kAlign));
+  unsigned long long* ticket = reinterpret_cast<unsigned long long*>(
+      reinterpret_cast<char*>(tbuf) + round_up((size_t)B * sizeof(float), kAlign));
   const hipStream_t s = static_cast<hipStream_t>(stream);
   const int nch = cats::fused_nch(bf16, d);
   const int bt_max = cats::fused_bt_max(bf16, nch);
@@ -1111,7 +1118,7 @@ cats_status cats_mlp_forward_topk(const cats_layer* layer, const float* x, int32
     e = cats::launch_row_select(vbuf, B, m, rank, tbuf, s);
     if (e != hipSuccess) return hip_fail(e, "per-row cutoff launch");
   }
-  st = run_mlp(layer, x, B, 0.f, false, residual, y, aux, ws, base, stream, false, 0.f, vbuf, tbuf);
+  st = run_mlp(layer, x, B, 0.f, false, residual, y, aux, ws, base, stream, false, 0.f, vbuf, tbuf, t_out);
   if (st != CATS_OK) return st;
   return sync_check(stream, "cats_mlp_forward_topk");
 }

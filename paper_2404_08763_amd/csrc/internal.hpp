@@ -85,6 +85,11 @@ struct ReduceArgs {
   int* active_cnt;
   float* active_v;
   float* active_h;
+  // copied on the way (top-k: the cutoffs to the caller's array, which no
+  // kernel of the call reads or has written before); null when not asked for
+  const float* t_src = nullptr;
+  float* t_dst = nullptr;
+  int t_n = 0;
 };
 
 // Instantiated chunk counts per row (NCH); a row of d elements uses the

@@ -43,6 +43,7 @@ __global__ __launch_bounds__(kReduceThreads) void k_mlp_reduce(ReduceArgs a) {
   const int d4 = a.d >> 2;
   const int ncb = (d4 + reduce_cols(a.G) - 1) / reduce_cols(a.G);
   const int nred = a.sum_y ? a.B * ncb : 0;
+  if (a.t_dst && blockIdx.x == 0 && tid < a.t_n) a.t_dst[tid] = a.t_src[tid];
 
   if ((int)blockIdx.x < nred && a.G <= kReduceFew) {
     // y[b, c] = residual[b, c] + (s_0 + s_1) + (s_2 + s_3), s_r = the sum over k

@@ -159,3 +159,21 @@ def test_topk_rejects_bad_sparsity(small_bf16):
     for k in (-0.1, 1.5, float("nan")):
         with pytest.raises(P.CatsError):
             P.mlp_forward_topk(layer, x, k)
+
+
+@pytest.mark.parametrize("B", [1, 3, 11])
+def test_topk_cutoffs_leave_last(small_bf16, B):
+    """The call's kernels take the cutoffs from its workspace, and the caller's
+    array is written by the last launch alone: shared with other calls, or (here)
+    lying where x was, it changes nothing of y."""
+    layer, _ = small_bf16
+    x = torch.from_numpy(_x(B, 1032, seed=25)).cuda()
+    y, t = P.mlp_forward_topk(layer, x, 0.6)
+    say("topk cutoffs leave last B", B)
+    L = P.raw()
+    ws = torch.zeros(int(L.cats_topk_workspace_bytes(1032, 693, B)), dtype=torch.uint8, device="cuda")
+    got = torch.empty_like(y)
+    assert L.cats_mlp_forward_topk(layer.c, x.data_ptr(), B, 0.6, None, got.data_ptr(), None, ws.data_ptr(),
+                                   ws.numel(), torch.cuda.current_stream().cuda_stream, x.data_ptr()) == 0
+    assert torch.equal(got.view(torch.int32), y.view(torch.int32))
+    assert torch.equal(x.flatten()[:B].view(torch.int32), t.view(torch.int32))
