@@ -90,6 +90,7 @@ struct ReduceArgs {
   const float* t_src = nullptr;
   float* t_dst = nullptr;
   int t_n = 0;
+  int few = 0;  // the sum's form (set by the launcher)
 };
 
 // Instantiated chunk counts per row (NCH); a row of d elements uses the
@@ -108,7 +109,9 @@ hipError_t launch_fused_bf16_dense(int nch, int bt, const FusedArgs& a, int G, h
 hipError_t launch_fused_f32_cats(int nch, int bt, const FusedArgs& a, int G, hipStream_t s);
 hipError_t launch_fused_f32_cats_aux(int nch, int bt, const FusedArgs& a, int G, hipStream_t s);
 hipError_t launch_fused_f32_dense(int nch, int bt, const FusedArgs& a, int G, hipStream_t s);
-hipError_t launch_reduce(const ReduceArgs& a, hipStream_t s);
+hipError_t launch_reduce(ReduceArgs a, hipStream_t s);
+// Whether the sum of G partials of that many outputs takes 16 columns per wave.
+bool reduce_few(int G, int outputs);
 
 // Top-k variant: gate activations of B <= 8 rows into v [B x m], the per-row
 // cutoffs (rank r of |v| within each row) into t [B], then the fused kernel

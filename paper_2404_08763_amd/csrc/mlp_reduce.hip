@@ -15,14 +15,26 @@ constexpr int kReduceThreads = 512;
 constexpr int kReduceWaves = kReduceThreads / kWaveSize;    // float4 columns per block
 constexpr int kReducePer = kFusedBlocks / kWaveSize;        // partials per lane
 static_assert(kFusedBlocks % kWaveSize == 0, "partials must split evenly over the lanes");
-// Up to kReduceFew partials (the batched path's neuron groups): a wave takes 16
-// consecutive float4 columns, its four rows of 16 lanes every fourth partial,
-// so each load covers four runs of 256 bytes; one column per wave would read
-// 16 bytes of each partial per lane and leave most lanes without one
-// (5120 columns, 25 partials, 16 rows: 4.0 us against 8.1).
+// Up to kReduceFew partials (the batched path's neuron groups, or blocks of few
+// neurons) of many outputs: a wave takes 16 consecutive float4 columns, its
+// four rows of 16 lanes every fourth partial, so each load covers four runs of
+// 256 bytes; one column per wave would read 16 bytes of each partial per lane
+// and leave most lanes without one (5120 columns, 25 partials, 16 rows: 4.0 us
+// against 8.1).
 constexpr int kReduceFew = 64;
 constexpr int kReduceFewCols = kReduceThreads / 4;
-__host__ __device__ constexpr int reduce_cols(int G) { return G <= kReduceFew ? kReduceFewCols : kReduceWaves; }
+__host__ __device__ constexpr int reduce_cols(int few) { return few ? kReduceFewCols : kReduceWaves; }
+
+// Many outputs: from 16384 on, where a column per wave takes two blocks per
+// compute unit and more.  Below that its blocks are all on the chip at once,
+// each lane with one load to wait for, where the 16-column form has a
+// sixteenth of the blocks and 16 loads a lane (us a call, one column / 16
+// columns per wave: 1032 x 64 at 1 / 3 rows 6.8 / 7.6 and 10.3 / 11.0,
+// 4096 x 64 at 3 rows 14.6 / 15.3, 3072 x 1000 at 5 rows 19.9 / 20.3; at
+// 16384 outputs, 2048 x 1000 at 8 rows, 18.7 / 18.8; above, 2304 x 1000 at 8
+// rows 22.6 / 22.0, 4096 x 1000 at 5 rows 23.1 / 22.2, 8192 x 40 at 3 rows
+// 23.1 / 22.5).
+bool reduce_few(int G, int outputs) { return G <= kReduceFew && outputs >= 16384; }
 // List finalize: entries per thread per pass, and one count per wave and
 // entry slot, which one wave scans.
 constexpr int kFinPer = 8;
@@ -41,11 +53,11 @@ __global__ __launch_bounds__(kReduceThreads) void k_mlp_reduce(ReduceArgs a) {
   const int tid = threadIdx.x;
   const int lane = tid & (kWaveSize - 1);
   const int d4 = a.d >> 2;
-  const int ncb = (d4 + reduce_cols(a.G) - 1) / reduce_cols(a.G);
+  const int ncb = (d4 + reduce_cols(a.few) - 1) / reduce_cols(a.few);
   const int nred = a.sum_y ? a.B * ncb : 0;
   if (a.t_dst && blockIdx.x == 0 && tid < a.t_n) a.t_dst[tid] = a.t_src[tid];
 
-  if ((int)blockIdx.x < nred && a.G <= kReduceFew) {
+  if ((int)blockIdx.x < nred && a.few) {
     // y[b, c] = residual[b, c] + (s_0 + s_1) + (s_2 + s_3), s_r = the sum over k
     // ascending of partial[4 k + r, b, c]
     const int b = blockIdx.x / ncb, cb = blockIdx.x - b * ncb;
@@ -232,9 +244,10 @@ __global__ __launch_bounds__(kReduceThreads) void k_mlp_reduce(ReduceArgs a) {
   if (tid == 0 && a.active_cnt && part == nfb - 1) a.active_cnt[b] = run;
 }
 
-hipError_t launch_reduce(const ReduceArgs& a, hipStream_t s) {
+hipError_t launch_reduce(ReduceArgs a, hipStream_t s) {
+  a.few = reduce_few(a.G, a.B * a.d) ? 1 : 0;
   const int d4 = a.d >> 2;
-  const int ncb = (d4 + reduce_cols(a.G) - 1) / reduce_cols(a.G);
+  const int ncb = (d4 + reduce_cols(a.few) - 1) / reduce_cols(a.few);
   const int grid = (a.sum_y ? a.B * ncb : 0) + (a.aux ? a.B * fin_blocks(a.m) : 0);
   if (grid == 0) return hipSuccess;
   KernelTimer timer("k_mlp_reduce", s);

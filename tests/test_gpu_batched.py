@@ -30,6 +30,8 @@ SHAPES = [
     (1088, 23100, 4),
     (1024, 28000, 4),
     (8, 65536, 5),       # the most neurons, the narrowest rows
+    (2048, 1000, 8),     # the sum of few partials at its fewest outputs
+    (2040, 1000, 8),     # and one column per wave below them
 ]
 
 
