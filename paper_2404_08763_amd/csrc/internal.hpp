@@ -165,6 +165,8 @@ hipError_t launch_unfused_down(int wdtype_bf16, int nch, int bt, bool index, con
 // split into, and whether a call of B rows takes it.
 int batch_planes(int d, int B);
 bool batched_rows(int d, int m, int B);
+// Tiles of 16 neurons of a gate/up step (dense: gate and up tiles).
+int gateup_tiles(int m, int B, bool dense);
 hipError_t launch_gateup(bool dense, int planes, const GateUpArgs& a, int G, hipStream_t s);
 hipError_t launch_down(int planes, const DownArgs& a, hipStream_t s);
 hipError_t launch_sparse_input(const SparseInputArgs& a, hipStream_t s);

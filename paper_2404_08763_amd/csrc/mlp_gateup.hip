@@ -72,7 +72,9 @@ struct GuGeom {
   static constexpr int OPS = 2 * T + XI;
   static constexpr int FIT = 144 * 1024 / SB;
   static constexpr int BUFS = FIT > 8 ? 8 : FIT;
-  static constexpr int VROWS = T < 6 ? 16 * T : kFusedMaxNeurons;  // neurons of a block (below 6 tiles: one round)
+  // neurons of a block: up to three tiles a step one round, four tiles two at
+  // most (gateup_tiles)
+  static constexpr int VROWS = T < 4 ? 16 * T : (T == 4 ? 128 : kFusedMaxNeurons);
   static_assert(BUFS >= 2 && (BUFS - 1) * OPS < 64, "two steps must fit, and vmcnt is six bits");
 };
 
@@ -442,8 +444,6 @@ template <int T, bool DENSE>
 static hipError_t launch_gateup_t(int planes, const GateUpArgs& a, int G, hipStream_t s) {
   KernelTimer timer(DENSE ? "mlp_gateup_dense" : "mlp_gateup_cats", s);
   const dim3 grid(G), block(GuGeom<T, 2, 8>::THREADS);
-  // (eight tiles and 16 rows of x leave no room for a second step)
-  constexpr int T16 = T > 6 ? 6 : T;
 #define CATS_GU(TT, NS, XR, STREAM) \
   hipExtLaunchKernelGGL((k_mlp_gateup<TT, NS, XR, DENSE, STREAM>), grid, block, 0, s, timer.start(), timer.stop(), 0, a)
   // Non-temporal reads for rows of whole lines in blocks that the 256 MB
@@ -458,29 +458,48 @@ static hipError_t launch_gateup_t(int planes, const GateUpArgs& a, int G, hipStr
     else if (planes == 2) CATS_GU(T, 2, 8, false);
     else if (stream) CATS_GU(T, 3, 8, true);
     else CATS_GU(T, 3, 8, false);
+  } else if constexpr (T <= 6) {  // (eight tiles and 16 rows of x leave no room for a second step)
+    if (planes == 2 && stream) CATS_GU(T, 2, 16, true);
+    else if (planes == 2) CATS_GU(T, 2, 16, false);
+    else if (stream) CATS_GU(T, 3, 16, true);
+    else CATS_GU(T, 3, 16, false);
   } else {
-    if (planes == 2 && stream) CATS_GU(T16, 2, 16, true);
-    else if (planes == 2) CATS_GU(T16, 2, 16, false);
-    else if (stream) CATS_GU(T16, 3, 16, true);
-    else CATS_GU(T16, 3, 16, false);
+    return hipErrorInvalidValue;
   }
 #undef CATS_GU
   return hipGetLastError();
 }
 
+// Tiles of a step: the fewest rounds over the block's neurons that eight (up to
+// 8 rows) or six tiles a step allow, and of the steps that need no more rounds
+// the smallest, whose pipeline is deeper and which multiplies fewer missing
+// tiles.  A dense step holds gate and up tiles.  us a call with steps as large as
+// they go / so: 28672 neurons (seven tiles) at 9 rows, k = 0.5: 1024 columns 53 / 47,
+// 4096 columns 138 / 123; dense 20000 neurons (five) at 4 rows of 4096 columns
+// 96 / 88, 14336 neurons (four) at 9 rows of 5120 columns 92 / 85.
+int gateup_tiles(int m, int B, bool dense) {
+  const int G = fused_grid(m);
+  const int tiles = ((m + G - 1) / G + 15) / 16;  // of the largest block
+  const int most = (B > 8 ? 6 : 8) / (dense ? 2 : 1);
+  const int rounds = (tiles + most - 1) / most;
+  const int per = (tiles + rounds - 1) / rounds;
+  if (dense) return 2 * per;
+  return per == 5 ? 6 : (per == 7 ? 8 : per);
+}
+
 hipError_t launch_gateup(bool dense, int planes, const GateUpArgs& a, int G, hipStream_t s) {
-  const int tiles = ((a.m + G - 1) / G + 15) / 16;  // of the largest block
+  const int T = gateup_tiles(a.m, a.B, dense);
   if (dense) {
-    if (tiles <= 1) return launch_gateup_t<2, true>(planes, a, G, s);
-    if (tiles == 2) return launch_gateup_t<4, true>(planes, a, G, s);
-    if (tiles == 3) return launch_gateup_t<6, true>(planes, a, G, s);
+    if (T == 2) return launch_gateup_t<2, true>(planes, a, G, s);
+    if (T == 4) return launch_gateup_t<4, true>(planes, a, G, s);
+    if (T == 6) return launch_gateup_t<6, true>(planes, a, G, s);
     return launch_gateup_t<8, true>(planes, a, G, s);
   }
-  if (tiles <= 1) return launch_gateup_t<1, false>(planes, a, G, s);
-  if (tiles == 2) return launch_gateup_t<2, false>(planes, a, G, s);
-  if (tiles == 3) return launch_gateup_t<3, false>(planes, a, G, s);
-  if (tiles == 4) return launch_gateup_t<4, false>(planes, a, G, s);
-  if (tiles <= 6) return launch_gateup_t<6, false>(planes, a, G, s);
+  if (T == 1) return launch_gateup_t<1, false>(planes, a, G, s);
+  if (T == 2) return launch_gateup_t<2, false>(planes, a, G, s);
+  if (T == 3) return launch_gateup_t<3, false>(planes, a, G, s);
+  if (T == 4) return launch_gateup_t<4, false>(planes, a, G, s);
+  if (T == 6) return launch_gateup_t<6, false>(planes, a, G, s);
   return launch_gateup_t<8, false>(planes, a, G, s);
 }
 

@@ -29,3 +29,26 @@ def test_sum_of_few_partials(d, G, B, one, sixteen):
     few = _rule("_ZN4cats10reduce_fewEii", I, I)
     assert few(G, B * d) == (sixteen < one)
     assert not few(65, B * d)
+
+
+@pytest.mark.parametrize("dense", [False, True])
+@pytest.mark.parametrize("B", [3, 8, 9, 16])
+def test_gateup_tiles(B, dense):
+    """The tiles of a gate/up step: instantiated, no more rounds than the
+    largest step needs, and within the neurons a block's LDS arrays hold."""
+    f = P.raw()._ZN4cats12gateup_tilesEiib
+    f.argtypes = [I, I, ctypes.c_bool]
+    for m in (1, 255, 256, *range(257, 65537, 37), 65536):
+        nb = -(-m // min(m, 256))
+        T = f(m, B, dense)
+        most = 6 if B > 8 else 8
+        assert T in ((2, 4, 6, 8) if dense else (1, 2, 3, 4, 6, 8)) and T <= most
+        cols = 16 * T // (2 if dense else 1)
+        rounds = -(-nb // cols)
+        assert rounds == -(-nb // (16 * most // (2 if dense else 1)))
+        if not dense and T <= 4:
+            assert rounds == 1 or (T == 4 and nb <= 128)
+    # rows of x, neurons, tiles a step where both were timed
+    for rows, m, d_, T in ((9, 28672, False, 4), (16, 28672, False, 4), (8, 28672, False, 8), (9, 14336, True, 4),
+                           (4, 20000, True, 6), (8, 34000, False, 6)):
+        assert f(m, rows, d_) == T

@@ -30,6 +30,10 @@ SHAPES = [
     (1088, 23100, 4),
     (1024, 28000, 4),
     (8, 65536, 5),       # the most neurons, the narrowest rows
+    (264, 28672, 16),    # seven tiles: two rounds of four (dense: three of three)
+    (1088, 28700, 9),    # eight tiles less fifteen neurons
+    (136, 17000, 8),     # five tiles (dense: two rounds of three)
+    (136, 34000, 12),    # nine tiles: two rounds of six
     (2048, 1000, 8),     # the sum of few partials at its fewest outputs
     (2040, 1000, 8),     # and one column per wave below them
 ]
