@@ -161,10 +161,13 @@ hipError_t launch_unfused_up(int wdtype_bf16, int nch, int bt, bool index, const
 hipError_t launch_unfused_down(int wdtype_bf16, int nch, int bt, bool index, const UnfusedArgs& a, int G,
                                hipStream_t s);
 
-// The batched path (mlp_gateup.hip, mlp_down.hip): the bf16 planes x and h are
+// The batched path (mlp_gateup.hip, mlp_gateup_narrow.hip, mlp_down.hip): the bf16 planes x and h are
 // split into, and whether a call of B rows takes it.
 int batch_planes(int d, int B);
 bool batched_rows(int d, int m, int B);
+// Whether the gate/up kernel with x in registers takes a two-plane block.
+bool gateup_narrow(int d, int m, bool dense);
+hipError_t launch_gateup_narrow(bool dense, const GateUpArgs& a, int G, hipStream_t s);
 // Tiles of 16 neurons of a gate/up step (dense: gate and up tiles).
 int gateup_tiles(int m, int B, bool dense);
 hipError_t launch_gateup(bool dense, int planes, const GateUpArgs& a, int G, hipStream_t s);

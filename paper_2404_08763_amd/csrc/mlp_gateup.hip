@@ -488,6 +488,7 @@ int gateup_tiles(int m, int B, bool dense) {
 }
 
 hipError_t launch_gateup(bool dense, int planes, const GateUpArgs& a, int G, hipStream_t s) {
+  if (planes == 2 && gateup_narrow(a.d, a.m, dense)) return launch_gateup_narrow(dense, a, G, s);
   const int T = gateup_tiles(a.m, a.B, dense);
   if (dense) {
     if (T == 2) return launch_gateup_t<2, true>(planes, a, G, s);

@@ -52,3 +52,21 @@ def test_gateup_tiles(B, dense):
     for rows, m, d_, T in ((9, 28672, False, 4), (16, 28672, False, 4), (8, 28672, False, 8), (9, 14336, True, 4),
                            (4, 20000, True, 6), (8, 34000, False, 6)):
         assert f(m, rows, d_) == T
+
+
+# d, m, dense, us with k_mlp_gateup / with x in registers
+@pytest.mark.parametrize("d,m,dense,stream,narrow", [
+    (512, 3000, False, 15.4, 15.7), (512, 5632, False, 18.4, 17.6), (512, 28672, False, 34.6, 29.2),
+    (512, 60000, False, 59.0, 46.4), (1024, 5632, False, 19.3, 19.9), (1024, 8000, False, 23.6, 22.5),
+    (1024, 11008, False, 26.8, 23.7), (1024, 28672, False, 49.8, 43.0), (2048, 28672, False, 67.7, 70.0),
+    (2048, 34000, False, 86.2, 80.7),
+    (512, 11008, True, 19.3, 19.5), (512, 28672, True, 35.4, 30.6), (1024, 8000, True, 20.1, 21.2),
+    (1024, 18000, True, 33.0, 31.0), (2048, 28672, True, 66.6, 70.9),
+])
+def test_gateup_of_narrow_blocks(d, m, dense, stream, narrow):
+    f = _rule("_ZN4cats13gateup_narrowEiib", I, I, ctypes.c_bool)
+    assert f(d, m, dense) == (narrow < stream)
+    # x in registers pipelines from one of a block's tiles to the next
+    assert not narrow < stream or m // 256 > 16
+    for other in (d + 8, d - 8, 3072, 5120):  # widths that it has no instance for
+        assert not f(other, m, dense)

@@ -34,6 +34,12 @@ SHAPES = [
     (1088, 28700, 9),    # eight tiles less fifteen neurons
     (136, 17000, 8),     # five tiles (dense: two rounds of three)
     (136, 34000, 12),    # nine tiles: two rounds of six
+    (512, 9001, 6),      # x in registers: three tiles, a ragged last one
+    (1024, 8000, 16),    # its fewest neurons at 1024 columns
+    (512, 12300, 9),     # its fewest dense ones
+    (1024, 28672, 5),
+    (2048, 32800, 7),    # its widest, CATS only, more than eight tiles
+    (512, 65536, 16),    # the most neurons
     (2048, 1000, 8),     # the sum of few partials at its fewest outputs
     (2040, 1000, 8),     # and one column per wave below them
 ]
@@ -100,7 +106,8 @@ def test_batched_shapes(d, m, B):
     assert torch.equal(P.mlp_forward(layer, x, math.inf, residual=res, ws=ws), res)
 
 
-@pytest.mark.parametrize("d,m,B", [(4096, 300, 8), (2856, 3000, 7), (1032, 3000, 16), (5128, 700, 4)])
+@pytest.mark.parametrize("d,m,B", [(4096, 300, 8), (2856, 3000, 7), (1032, 3000, 16), (5128, 700, 4), (512, 5000, 8),
+                                   (1024, 8000, 11)])
 def test_batched_rmsnorm(d, m, B):
     P = _P()
     w, x, _ = _inputs(d, m, B, 3)
