@@ -215,7 +215,7 @@ cats_status run_mlp(const cats_layer* L, const float* x, int32_t B, float t, boo
   const hipStream_t s = static_cast<hipStream_t>(stream);
   const int G = cats::fused_grid(m);
   const int planes = cats::batch_planes(d, B);
-  if (!vin && bf16 && cats::batched_rows(d, m, B)) {
+  if (!vin && bf16 && cats::batched_rows(d, m, B, dense)) {
     // all rows in one pass: gate/up on the matrix cores, down by column tiles
     cats::GateUpArgs ba{};
     ba.wg = L->w_gate_t;
@@ -484,31 +484,48 @@ static bool two_plane_width(int d) {
 int batch_planes(int d, int B) { return B >= 5 && two_plane_width(d) ? 2 : 3; }
 
 // Whether the matrix-core path (three launches) takes a call, or the fused
-// kernel (two, its products on the vector ALUs).
+// kernel (two, its products on the vector ALUs).  us a call, fused / matrix
+// cores, blocks in turn (weights of many such blocks do not stay in L2).
 // One and two rows: the fused kernel, whose dot products keep up with the
-// weights (2 rows, us, fused / matrix cores: 4096 x 11008 40 / 45).
+// weights (2 rows at 4096 x 11008 40 / 45).
 // Three and four rows: it keeps up while x's rows leave it two waves per SIMD,
 // up to d = 5120 (3 rows at 4096 x 11008: 49.0 / 50.3); above that the matrix
 // cores are faster but for the smallest blocks (8192 x 28672 at k = 0.5, 3 rows
-// 251 / 208, 4 rows 296 / 222; 6144 x 2000, 3 rows 41 / 32; 5640 x 600, 3 rows
-// 30.0 / 29.1; 8192 x 512, 3 rows 31.6 / 33.2, 4 rows 37.7 / 33.4).  Four rows
-// of whole 128-byte lines of weights also where reading them outweighs the
-// third launch (5120 x 13824 88 / 82; 4096 x 11008 54.0 / 52.1; 4096 x 6200
-// 41.2 / 38.8; 1024 x 28000 58 / 45; rows that end inside a line are read
-// better by the fused kernel: 2856 x 20000 78 / 86).
+// 251 / 208, 4 rows 296 / 222; 6144 x 2000, 3 rows 44.1 / 33.8; 8192 x 512, 3
+// rows 36.2 / 34.7; 5640 x 128, 3 rows 26.9 / 29.3).  Four rows of whole 128-byte
+// lines of weights also where reading them outweighs the third launch
+// (5120 x 13824 88 / 82; 4096 x 11008 54.0 / 52.1; 4096 x 6200 41.2 / 38.8;
+// 1024 x 28000 58 / 45; rows that end inside a line are read better by the
+// fused kernel: 2856 x 20000 78 / 86), except CATS with more than eight tiles
+// of neurons a block at more than 1024 columns (4096 x 34000 135 / 146;
+// 1024 x 34000 67 / 56).
 // From 5 rows the fused kernel is faster only for small narrow blocks, where a
-// launch weighs more than the products (512 x 1408 at 5 rows 12.5 / 15.3, at 8
-// rows 14.6 / 15.3; 1024 x 1024 at 5 rows 15.0 / 17.4; 512 x 3000 at 5 rows
-// 15.4 / 15.8, at 8 rows 18.2 / 16.0; 1024 x 2048 at 6 rows 17.4 / 16.6;
-// 1000 x 3000 at 5 rows 19.2 / 18.0).  At the three-plane widths small blocks
-// keep the fused kernel at every row count: there the forward is bit for bit
-// the separate kernels' result (cats_mlp_forward_unfused).
-bool batched_rows(int d, int m, int B) {
+// launch, and with CATS the change from gate to up tiles, weighs more than the
+// products.  Dense: 256 x 2000 at 8 rows 14.2 / 13.9, at 5 rows 12.6 / 13.8;
+// 520 x 4000 at 5 rows 18.6 / 16.0.  CATS, k = 0.9: up to 512 columns by the
+// neurons of all rows (256 x 3000 at 6 / 8 rows 14.0 / 15.5 and 15.5 / 15.7); above,
+// with 5 and 6 rows, also while a block has one neuron per wave of the fused
+// kernel (1000 x 2000 at 5 rows 16.3 / 18.4, 1000 x 2500 17.9 / 18.0; 776 x 2000 at
+// 6 rows 16.4 / 18.1; 776 x 3000 at 5 rows 17.1 / 17.9, 1000 x 4000 19.3 / 19.2).
+// At the three-plane widths small blocks keep the fused kernel at every row
+// count: there the forward is bit for bit the separate kernels' result
+// (cats_mlp_forward_unfused).  That, not the time, sets the line from 9 rows
+// on, where the fused kernel needs two passes (256 x 1000 at 9 / 16 rows
+// 19.3 / 15.0 and 24.1 / 15.1; 1032 x 512 at 16 rows 45.6 / 19.2).
+bool batched_rows(int d, int m, int B, bool dense) {
   const int64_t md = (int64_t)m * d;
   if (B < 3) return false;
-  if (B < 5) return d > 5120 ? B * md >= 10000000 : B == 4 && d % 64 == 0 && md >= 25000000;
-  if ((int64_t)B * m * (d < 512 ? 512 : d) > 8000000) return true;
-  return two_plane_width(d) && (B > 8 || d > 1024);
+  if (B < 5) {
+    if (d > 5120) return B * md >= 10000000;
+    return B == 4 && d % 64 == 0 && md >= 25000000 && (dense || d <= 1024 || m <= 8 * 16 * kFusedBlocks);
+  }
+  if (two_plane_width(d) && (B > 8 || d > 1024)) return true;
+  const int64_t work = (int64_t)B * m * (d < 512 ? 512 : d);
+  if (work <= 8000000) return false;
+  if (dense || B > 8 || d > 2048) return true;
+  if (d <= 512) return B * m > 21000;
+  if (B == 5) return m > 2048 && work > 12000000;
+  return B > 6 || d > 1024 || m > 2048;
 }
 
 int fused_grid(int m) { return m < kFusedBlocks ? m : kFusedBlocks; }

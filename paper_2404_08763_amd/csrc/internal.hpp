@@ -164,7 +164,7 @@ hipError_t launch_unfused_down(int wdtype_bf16, int nch, int bt, bool index, con
 // The batched path (mlp_gateup.hip, mlp_gateup_narrow.hip, mlp_down.hip): the bf16 planes x and h are
 // split into, and whether a call of B rows takes it.
 int batch_planes(int d, int B);
-bool batched_rows(int d, int m, int B);
+bool batched_rows(int d, int m, int B, bool dense);
 // Whether the gate/up kernel with x in registers takes a two-plane block.
 bool gateup_narrow(int d, int m, bool dense);
 hipError_t launch_gateup_narrow(bool dense, const GateUpArgs& a, int G, hipStream_t s);

@@ -450,8 +450,10 @@ static hipError_t launch_gateup_t(int planes, const GateUpArgs& a, int G, hipStr
   // last-level cache cannot hold two of.  From memory they are 5 to 10%
   // faster (4096 x 11008 dense at 16 rows 37.0 us cached, 32.4 so; 24 blocks of
   // 2048 x 5632 in turn 29.7 / 28.3 a call), from that cache 7% slower (three
-  // such blocks in turn 25.5 / 27.9); where lines straddle rows and steps they
-  // fetch them twice (2856 x 7001 at 11 rows 22.2 / 28.1).
+  // such blocks in turn 25.5 / 27.9; a larger block called again and again by
+  // itself, of which k = 0.9 leaves the cache little to hold: 2048 x 28672 at 9
+  // rows 58 / 61); where lines straddle rows and steps they fetch them twice
+  // (2856 x 7001 at 11 rows 22.2 / 28.1).
   const bool stream = a.d % 64 == 0 && (uint64_t)a.m * a.d * 6 >= (144ull << 20);
   if (a.B <= 8) {
     if (planes == 2 && stream) CATS_GU(T, 2, 8, true);

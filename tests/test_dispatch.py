@@ -70,3 +70,32 @@ def test_gateup_of_narrow_blocks(d, m, dense, stream, narrow):
     assert not narrow < stream or m // 256 > 16
     for other in (d + 8, d - 8, 3072, 5120):  # widths that it has no instance for
         assert not f(other, m, dense)
+
+
+# d, m, rows, dense, us with the fused kernel / on the matrix cores
+@pytest.mark.parametrize("d,m,B,dense,fused,mfma", [
+    (4096, 11008, 2, False, 40, 45), (4096, 11008, 3, False, 49.0, 50.3), (8192, 28672, 3, False, 251, 208),
+    (6144, 2000, 3, False, 44.1, 33.8), (8192, 512, 3, False, 36.2, 34.7), (5640, 128, 3, False, 26.9, 29.3),
+    (8192, 512, 4, True, 41.9, 25.3), (4096, 11008, 4, False, 54.0, 52.1), (1024, 28000, 4, False, 58, 45),
+    (2856, 20000, 4, False, 78, 86), (4096, 34000, 4, False, 135, 146), (4096, 34000, 4, True, 140, 139),
+    (2048, 34000, 4, False, 84, 87), (1024, 34000, 4, False, 67, 56),
+    (256, 2000, 8, True, 14.2, 13.9), (256, 2000, 5, True, 12.6, 13.8), (520, 4000, 5, True, 18.6, 16.0),
+    (256, 2000, 8, False, 13.7, 15.6), (64, 3000, 6, False, 13.3, 14.4), (256, 3000, 6, False, 14.0, 15.5),
+    (512, 2000, 8, False, 14.8, 16.7), (136, 4000, 8, False, 17.4, 15.5), (1000, 2000, 5, False, 16.3, 18.4),
+    (1024, 2000, 5, False, 15.5, 16.8), (1000, 4000, 5, False, 19.3, 19.2), (776, 2000, 6, False, 16.4, 18.1),
+    (776, 2500, 6, False, 18.4, 17.8), (1032, 2000, 6, False, 20.2, 19.3), (776, 3000, 5, False, 17.1, 17.9),
+    (1032, 1000, 8, False, 23.3, 18.6), (776, 2000, 8, False, 19.4, 18.3), (2056, 1000, 5, False, 27.7, 21.6),
+    (256, 3000, 9, False, 23.8, 15.6), (8192, 28672, 8, True, 587, 224),
+])
+def test_batched_rows(d, m, B, dense, fused, mfma):
+    f = _rule("_ZN4cats12batched_rowsEiiib", I, I, I, ctypes.c_bool)
+    assert f(d, m, B, dense) == (mfma < fused)
+
+
+@pytest.mark.parametrize("B", [5, 8, 9, 16])
+@pytest.mark.parametrize("d,m", [(1032, 693), (264, 1000), (8, 65536), (4104, 100)])
+def test_small_three_plane_blocks_stay_fused(d, m, B):
+    """Where the forward is bit for bit the separate kernels' result."""
+    f = _rule("_ZN4cats12batched_rowsEiiib", I, I, I, ctypes.c_bool)
+    if B * m * max(d, 512) <= 8_000_000:
+        assert not f(d, m, B, False) and not f(d, m, B, True)
