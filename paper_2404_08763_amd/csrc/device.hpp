@@ -26,10 +26,12 @@ template <> struct wtraits<wf32> {
   static constexpr int VEC = 4;
 };
 
-// Byte offset that lies outside every buffer the kernels address: a
-// buffer load at (a sum of at most two of) these offsets returns zeros and
-// moves no data.  Buffers are limited to kBufMaxBytes so that a valid offset
-// plus one kOOB never wraps back into range.
+// Byte offset that lies outside every buffer the kernels address: a buffer
+// load at a sum of one to three of these (row, column and step each out of
+// range) and a valid offset returns zeros and moves no data.  Buffers are
+// limited to kBufMaxBytes, a quarter of the 32-bit range, so that a valid
+// offset plus three kOOB stays below 2^32 and never wraps back into range; a
+// fourth would.
 constexpr uint32_t kOOB = 0x40000000u;
 constexpr uint64_t kBufMaxBytes = 0x40000000ull;
 

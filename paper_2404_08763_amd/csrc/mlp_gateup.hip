@@ -70,12 +70,11 @@ struct GuGeom {
   static constexpr int WB = T * 2048 + XI * 1024;           // LDS bytes of a wave and step
   static constexpr int SB = W * WB;
   static constexpr int OPS = 2 * T + XI;
-  static constexpr int FIT = 144 * 1024 / SB;
-  static constexpr int BUFS = FIT > 8 ? 8 : FIT;
+  static constexpr int BUFS = 144 * 1024 / SB;              // steps in LDS at once
   // neurons of a block: up to three tiles a step one round, four tiles two at
   // most (gateup_tiles)
   static constexpr int VROWS = T < 4 ? 16 * T : (T == 4 ? 128 : kFusedMaxNeurons);
-  static_assert(BUFS >= 2 && (BUFS - 1) * OPS < 64, "two steps must fit, and vmcnt is six bits");
+  static_assert(BUFS >= 2 && BUFS <= 4 && (BUFS - 1) * OPS < 64, "two to four steps, and vmcnt is six bits");
 };
 
 // STREAM: the weights are read with the non-temporal policy.
@@ -91,8 +90,6 @@ __global__ __launch_bounds__((GuGeom<T, NS, XR>::THREADS)) void k_mlp_gateup(Gat
   // read depends on
   __shared__ __attribute__((aligned(1024))) uint8_t s0[SB], s1[SB];
   __shared__ __attribute__((aligned(1024))) uint8_t s2[BUFS > 2 ? SB : 16], s3[BUFS > 3 ? SB : 16];
-  __shared__ __attribute__((aligned(1024))) uint8_t s4[BUFS > 4 ? SB : 16], s5[BUFS > 5 ? SB : 16];
-  __shared__ __attribute__((aligned(1024))) uint8_t s6[BUFS > 6 ? SB : 16], s7[BUFS > 7 ? SB : 16];
   __shared__ float l_v[DENSE ? 1 : G::VROWS][XR];
   __shared__ uint32_t l_mask[DENSE ? 1 : G::VROWS];
   __shared__ int l_act[DENSE ? 1 : G::VROWS];  // the block's active neurons, ascending
@@ -265,13 +262,9 @@ __global__ __launch_bounds__((GuGeom<T, NS, XR>::THREADS)) void k_mlp_gateup(Gat
       issue(s1, c + 1);
       if constexpr (BUFS > 2) issue(s2, c + 2);
       if constexpr (BUFS > 3) issue(s3, c + 3);
-      if constexpr (BUFS > 4) issue(s4, c + 4);
-      if constexpr (BUFS > 5) issue(s5, c + 5);
-      if constexpr (BUFS > 6) issue(s6, c + 6);
-      if constexpr (BUFS > 7) issue(s7, c + 7);
       // whole rounds of the buffers in a loop without exits (with one after
       // each step the compiler loses count at the loop's head and waits for
-      // every load there), then the last steps
+      // every load there), then the last steps, fewer than the buffers
       for (; c + BUFS <= c1; c += BUFS) {
         constexpr Const<BUFS - 1> left;
         constexpr Const<1> more;
@@ -279,19 +272,11 @@ __global__ __launch_bounds__((GuGeom<T, NS, XR>::THREADS)) void k_mlp_gateup(Gat
         step(s1, c + 1, left, more);
         if constexpr (BUFS > 2) step(s2, c + 2, left, more);
         if constexpr (BUFS > 3) step(s3, c + 3, left, more);
-        if constexpr (BUFS > 4) step(s4, c + 4, left, more);
-        if constexpr (BUFS > 5) step(s5, c + 5, left, more);
-        if constexpr (BUFS > 6) step(s6, c + 6, left, more);
-        if constexpr (BUFS > 7) step(s7, c + 7, left, more);
       }
       constexpr Const<0> last;
       if (c < c1) step(s0, c, Const<BUFS - 1>(), last);
-      if (c + 1 < c1) step(s1, c + 1, Const<BUFS - 2>(), last);
-      if constexpr (BUFS > 2) { if (c + 2 < c1) step(s2, c + 2, Const<BUFS - 3>(), last); }
-      if constexpr (BUFS > 3) { if (c + 3 < c1) step(s3, c + 3, Const<BUFS - 4>(), last); }
-      if constexpr (BUFS > 4) { if (c + 4 < c1) step(s4, c + 4, Const<BUFS - 5>(), last); }
-      if constexpr (BUFS > 5) { if (c + 5 < c1) step(s5, c + 5, Const<BUFS - 6>(), last); }
-      if constexpr (BUFS > 6) { if (c + 6 < c1) step(s6, c + 6, Const<BUFS - 7>(), last); }
+      if constexpr (BUFS > 2) { if (c + 1 < c1) step(s1, c + 1, Const<BUFS - 2>(), last); }
+      if constexpr (BUFS > 3) { if (c + 2 < c1) step(s2, c + 2, Const<BUFS - 3>(), last); }
     }
     wait_vm<0>();  // no load is on its way to LDS any more
     wait_lds();
