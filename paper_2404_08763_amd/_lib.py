@@ -10,7 +10,7 @@ from __future__ import annotations
 import ctypes
 import os
 from dataclasses import dataclass
-from typing import Optional
+from typing import Callable, Optional
 
 # torch is imported first so that libcats binds to the HIP runtime torch
 # already loaded (both carry the soname libamdhip64.so.7); loading libcats
@@ -120,10 +120,18 @@ def _check(status: int) -> None:
         raise CatsError(status, msg)
 
 
-def _stream() -> int:
-    """The current stream of the current device, as torch keeps it: the handle
-    itself, without a Stream object around it (2.9 us of a call's 11)."""
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+def _stream_of_torch() -> Callable[[], int]:
+    """What returns the current stream's handle: torch's own record of it,
+    without a Stream object around it (2.9 us of a call's 11), or torch's public
+    call where this torch does not have those two functions."""
+    raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    device = getattr(torch._C, "_cuda_getDevice", None)
+    if raw_stream is None or device is None:
+        return lambda: torch.cuda.current_stream().cuda_stream
+    return lambda: raw_stream(device())
+
+
+_stream = _stream_of_torch()
 
 
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:

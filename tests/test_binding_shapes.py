@@ -72,3 +72,21 @@ def test_well_shaped_host_tensors_fail_only_on_the_device_check():
     with pytest.raises(ValueError, match="device tensor"):
         P.mlp_forward(LAYER, _x(2, 64), 0.5, out=_x(2, 64), residual=_x(2, 64))
     assert _lib._rows_of(_x(64), 64) == 1
+
+
+def test_stream_handle_without_torchs_private_functions(monkeypatch):
+    """The two functions that the current stream's handle comes from are not
+    part of torch's public interface: without either of them its public call
+    is used."""
+    for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice"):
+        with monkeypatch.context() as m:
+            m.delattr(torch._C, name, raising=False)
+            m.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=7))
+            assert _lib._stream_of_torch()() == 7
+
+
+@pytest.mark.gpu
+def test_stream_handle_is_the_current_streams():
+    for s in (torch.cuda.default_stream(), torch.cuda.Stream()):
+        with torch.cuda.stream(s):
+            assert _lib._stream() == s.cuda_stream == torch.cuda.current_stream().cuda_stream
