@@ -132,3 +132,24 @@ def cfg(name):
 
 def ws_for(layer: P.Layer, B: int = 1, ncal: int = 0):
     return P.workspace(layer.d, layer.m, B, ncal)
+
+
+def kernels_of(call):
+    """Names of the kernels that call() launches (cats_timer_*)."""
+    P.timer_reset()
+    P.timer_enable(True)
+    try:
+        call()
+        torch.cuda.synchronize()
+    finally:
+        P.timer_enable(False)
+    return {name for name, (n, _) in P.timer_read().items() if n > 0}
+
+
+def path_of(call):
+    """"fused", "batched" or "narrow": which kernels a forward or dense call takes."""
+    k = kernels_of(call)
+    if "mlp_down" not in k:
+        assert any(n.startswith("mlp_fused") for n in k), k
+        return "fused"
+    return "narrow" if any(n.startswith("mlp_gateup_narrow") for n in k) else "batched"

@@ -14,7 +14,7 @@ import torch
 import paper_2404_08763_amd as P
 from paper_2404_08763_amd import workloads as W
 
-from gpu_util import device_layer, say
+from gpu_util import device_layer, path_of, say
 
 pytestmark = pytest.mark.gpu
 
@@ -43,13 +43,14 @@ def _same_lists(a1, a2, B, label):
             _same(a1[k][b, :n], a2[k][b, :n], f"{label} {k} row {b}")
 
 
-@pytest.mark.parametrize("B", [1, 4, 16])
+@pytest.mark.parametrize("B", [1, 3, 4, 16])
 def test_forward_deterministic(c2, B):
-    """B = 1 and 4: the fused kernel; B = 16: the matrix-core path."""
+    """B = 1 and 3: the fused kernel; B = 4 and 16: the matrix-core path."""
     c, layer = c2
     x = W.decode_vectors(c, B).cuda()
     t = 0.27
     ws = P.workspace(c.d, c.m, B)
+    assert path_of(lambda: P.mlp_forward(layer, x, t, ws=ws)) == ("fused" if B < 4 else "batched")
     say("determinism forward B", B)
     y1, a1 = P.mlp_forward(layer, x, t, ws=ws, aux=True)
     y2, a2 = P.mlp_forward(layer, x, t, ws=ws, aux=True)

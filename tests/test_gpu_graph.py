@@ -14,7 +14,7 @@ import torch
 import paper_2404_08763_amd as P
 from paper_2404_08763_amd import workloads as W
 
-from gpu_util import device_layer, say
+from gpu_util import device_layer, path_of, say
 
 pytestmark = pytest.mark.gpu
 
@@ -62,7 +62,7 @@ def _replay_check(label, call, x_static, y_static, eager, xs):
 
 @pytest.mark.parametrize("B", [1, 3, 8])
 def test_forward_graph(layers, B):
-    """B = 8 at d = 1024 takes the matrix-core path (three kernels)."""
+    """Small enough for the fused kernel at all three row counts."""
     layer = layers[0]
     t = 0.15
     x_static = torch.zeros((B, 1024), device="cuda")
@@ -72,6 +72,30 @@ def test_forward_graph(layers, B):
     _replay_check(f"forward B{B}", lambda: P.mlp_forward(layer, x_static, t, out=y_static, ws=ws),
                   x_static, y_static, lambda x: P.mlp_forward(layer, x, t, ws=ws_e),
                   _inputs(B, 1024, REPLAYS, 40 + B))
+
+
+@pytest.mark.parametrize("d,m,B,path", [
+    (1024, 2000, 8, "batched"),   # two planes, 8-row operands
+    (1024, 2000, 16, "batched"),  # 16-row operands
+    (1032, 3000, 8, "batched"),   # three planes
+    (5128, 700, 4, "batched"),    # up to four rows
+    (1024, 8000, 6, "narrow"),    # x in registers
+])
+def test_forward_graph_matrix_cores(d, m, B, path):
+    """The matrix-core path's three kernels, CATS and dense."""
+    g = torch.Generator(device="cuda").manual_seed(d + m)
+    layer = P.Layer(*[(torch.randn((m, d), generator=g, device="cuda") * 0.02).bfloat16() for _ in range(3)])
+    x_static = torch.zeros((B, d), device="cuda")
+    y_static = torch.empty_like(x_static)
+    ws = P.workspace(d, m, B)
+    ws_e = P.workspace(d, m, B)
+    xs = _inputs(B, d, REPLAYS, 45 + B)
+    assert path_of(lambda: P.mlp_forward(layer, xs[0], 0.15, ws=ws)) == path
+    assert path_of(lambda: P.mlp_dense(layer, xs[0], ws=ws)) in ("batched", "narrow")
+    _replay_check(f"forward {d}x{m} B{B}", lambda: P.mlp_forward(layer, x_static, 0.15, out=y_static, ws=ws),
+                  x_static, y_static, lambda x: P.mlp_forward(layer, x, 0.15, ws=ws_e), xs)
+    _replay_check(f"dense {d}x{m} B{B}", lambda: P.mlp_dense(layer, x_static, out=y_static, ws=ws),
+                  x_static, y_static, lambda x: P.mlp_dense(layer, x, ws=ws_e), xs)
 
 
 def test_stack_graph(layers):

@@ -14,7 +14,7 @@ import torch
 import paper_2404_08763_amd as P
 from paper_2404_08763_amd import workloads as W
 
-from gpu_util import Y_TOL, band_ok, check_forward, device_layer, h_bound, host_f32, quantile_t, say
+from gpu_util import Y_TOL, band_ok, check_forward, device_layer, h_bound, host_f32, path_of, quantile_t, say
 
 pytestmark = pytest.mark.gpu
 
@@ -178,10 +178,21 @@ def test_batch_rows_have_their_own_masks(dev, oracle32, B):
 
 
 # ------------------------------------------------ batched (matrix-core) path
-# bf16 weights, 5..16 rows and d of 512, 1024, 2048, 3072, 4096 or 5120
+# bf16 weights, 5..16 rows and d of 512, 1024, 2048, 3072, 4096 or 5120 (up to
+# 8 rows the smallest blocks at 512 and 1024 stay with the fused kernel)
 @pytest.mark.parametrize("d,m,B", [(512, 7, 5), (512, 300, 8), (1024, 693, 16), (1024, 693, 6), (3072, 500, 7),
                                    (4096, 1100, 16), (2048, 4111, 12), (5120, 700, 16), (5120, 2063, 5)])
 def test_batched_path_vs_oracle(dev, oracle32, d, m, B):
+    _batched_path(oracle32, d, m, B, "fused" if d <= 1024 and B <= 8 else "batched")
+
+
+@pytest.mark.parametrize("d,m,B,path", [(512, 4500, 5, "batched"), (512, 4999, 8, "batched"), (512, 5632, 5, "narrow"),
+                                        (512, 7001, 16, "narrow"), (1024, 2100, 6, "batched"), (1024, 8000, 7, "narrow")])
+def test_batched_path_of_narrow_blocks_vs_oracle(dev, oracle32, d, m, B, path):
+    _batched_path(oracle32, d, m, B, path)
+
+
+def _batched_path(oracle32, d, m, B, path):
     c = W.shrink(W.CONFIGS["C3"], d, m)
     wg, wu, wd = W.weights(d, m, torch.bfloat16, layer=6)
     layer = device_layer(wg, wu, wd)
@@ -190,6 +201,7 @@ def test_batched_path_vs_oracle(dev, oracle32, d, m, B):
     ref_all = oracle32.cats_mlp(x.numpy(), *hw, t=0.0)
     res = torch.randn((B, d), generator=torch.Generator().manual_seed(10))
     ws = P.workspace(d, m, B)
+    assert path_of(lambda: P.mlp_forward(layer, x.cuda(), 0.1, ws=ws)) == path
     for k in (0.0, 0.5, 0.9):
         t = quantile_t(np.abs(ref_all["v"]), k) if k > 0 else 0.0
         say("batched path d", d, "m", m, "B", B, "k", k, "t", t)

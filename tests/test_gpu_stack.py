@@ -20,7 +20,7 @@ import torch
 import paper_2404_08763_amd as P
 from paper_2404_08763_amd import workloads as W
 
-from gpu_util import Y_TIGHT, check_forward, device_layer, h_bound, host_f32, say
+from gpu_util import Y_TIGHT, check_forward, device_layer, h_bound, host_f32, path_of, say
 from oracle_pins import _analytic_quantile
 
 pytestmark = pytest.mark.gpu
@@ -56,10 +56,10 @@ SMALL_D, SMALL_M, SMALL_L = 1032, 693, 4
 SMALL_T = [0.05, 0.12, 0.2, 0.3]
 
 
-def _small_stack(d):
+def _small_stack(d, m=SMALL_M):
     layers, hws = [], []
     for l in range(SMALL_L):
-        wg, wu, wd = W.weights(d, SMALL_M, torch.bfloat16, layer=l)
+        wg, wu, wd = W.weights(d, m, torch.bfloat16, layer=l)
         layers.append(device_layer(wg, wu, wd))
         hws.append(host_f32(wg, wu, wd))
     return layers, hws
@@ -72,9 +72,15 @@ def small(dev):
 
 @pytest.fixture(scope="module")
 def small_mfma(dev):
-    """d = 1024: from 5 rows on, bf16 blocks of this width take the
-    matrix-core path, whose RMSNorm is applied inside its gate/up kernel."""
+    """d = 1024: at 16 rows the matrix-core path, whose RMSNorm is applied
+    inside its gate/up kernel; at 5 rows blocks this small stay fused."""
     return _small_stack(1024)
+
+
+@pytest.fixture(scope="module")
+def larger_mfma(dev):
+    """d = 1024 and enough neurons for the matrix-core path from 6 rows on."""
+    return _small_stack(1024, 2100)
 
 
 def _x0(B, d, seed=11):
@@ -105,8 +111,18 @@ def test_small_stack_teacher_forced(small, oracle32, B):
 
 @pytest.mark.parametrize("B", [5, 16])
 def test_small_stack_teacher_forced_mfma(small_mfma, oracle32, B):
-    layers, hws = small_mfma
+    _teacher_forced_1024(small_mfma, oracle32, B, "fused" if B == 5 else "batched")
+
+
+@pytest.mark.parametrize("B", [6, 8])
+def test_larger_stack_teacher_forced_mfma(larger_mfma, oracle32, B):
+    _teacher_forced_1024(larger_mfma, oracle32, B, "batched")
+
+
+def _teacher_forced_1024(stack, oracle32, B, path):
+    layers, hws = stack
     x0 = _x0(B, 1024, seed=14)
+    assert path_of(lambda: P.stack_forward(P.Stack(layers, SMALL_T), torch.from_numpy(x0).cuda(), eps=EPS)) == path
     xo, cnto = oracle32.stack(x0, hws, SMALL_T, eps=EPS)
     for l in range(SMALL_L):
         say("small stack (matrix-core path) B", B, "layer", l, "t", SMALL_T[l])
