@@ -127,22 +127,82 @@ def test_batched_rmsnorm(d, m, B):
 @pytest.mark.parametrize("d,m,B", [(1032, 3000, 8), (5128, 700, 4)])
 def test_batched_special_values(d, m, B):
     """Three planes: an infinity or NaN in one row spoils that row alone, as it
-    does in fp32 products, and large and tiny values lose nothing."""
+    does in fp32 products."""
     P = _P()
     w, x, _ = _inputs(d, m, B, 11)
     x[1, 7] = float("inf")
     x[2, 9] = float("nan")
-    x[3] *= 1e30
-    if B > 4:
-        x[4] *= 1e-30
     y = P.mlp_dense(P.Layer(*w), x)
     x64 = x.double()
     want = (_silu(x64 @ w[0].double().t()) * (x64 @ w[1].double().t())) @ w[2].double()
     assert not torch.isfinite(y[1]).any() and torch.isnan(y[2]).all()
-    for b in (0, *range(5, B)):
+    for b in (0, *range(3, B)):
         assert (y[b].double() - want[b]).norm() <= _bound(d, B) * want[b].norm()
-    fine = want[3].abs() < 1e38
-    assert (torch.isfinite(y[3]) | ~fine).all()
+
+
+def _two_planes(x):
+    hi = x.bfloat16().float()
+    return hi.double() + (x - hi).bfloat16().double()
+
+
+def _rel(a, b):
+    return ((a.double() - b).norm() / b.norm()).item()
+
+
+@pytest.mark.parametrize("d,m,B", [(1032, 3000, 8), (1032, 3000, 16), (5128, 700, 4)])
+def test_batched_three_planes_of_x(d, m, B):
+    """All 24 bits of x count, whatever its exponent: neighbouring channels of
+    nearly equal values meet opposite weights, so a product is what the low
+    bits differ by, and each pair is scaled by a power of two from 2^-60 to 2^60
+    that its weights undo.  What is left of a term is 2^-12 of it; fp32 sums round
+    2^-24 of a partial sum of some sqrt(d) terms, 2^-12 of the result a step and
+    2^-10 in all; two planes round each x by 2^-19 (root mean square), 2^-7 of a
+    gate or up result."""
+    P = _P()
+    g = torch.Generator(device="cuda").manual_seed(d + B)
+    r = torch.rand((B, d // 2), generator=g, device="cuda") + 0.5
+    x = torch.empty((B, d), device="cuda")
+    x[:, 0::2] = r
+    x[:, 1::2] = r - r * 2.0 ** -12 * (1 + torch.rand(r.shape, generator=g, device="cuda"))
+    e = torch.randint(-60, 61, (d // 2,), generator=g, device="cuda").repeat_interleave(2).double()
+    w = []
+    for _ in range(2):
+        half = (torch.randn((m, d // 2), generator=g, device="cuda") * 64).bfloat16()
+        full = torch.empty((m, d), dtype=torch.bfloat16, device="cuda")
+        full[:, 0::2], full[:, 1::2] = half, -half
+        w.append((full.double() * 2.0 ** -e).bfloat16())
+    w.append((torch.randn((m, d), generator=g, device="cuda") * 0.05).bfloat16())
+    xs = (x.double() * 2.0 ** e).float()
+
+    def ref(z):
+        return (_silu(z @ w[0].double().t()) * (z @ w[1].double().t())) @ w[2].double()
+
+    want = ref(xs.double())
+    got, two = _rel(P.mlp_dense(P.Layer(*w), xs), want), _rel(ref(_two_planes(xs)), want)
+    print(f"[planes] x {d}x{m} B{B}: {got:.2e}, two planes {two:.2e}")
+    assert got <= 2.0 ** -10 and two >= 2.0 ** -7
+
+
+@pytest.mark.parametrize("d,m,B", [(1032, 3000, 8), (1032, 3000, 16), (5128, 700, 4)])
+def test_batched_three_planes_of_h(d, m, B):
+    """All 24 bits of h count: pairs of neurons that differ in one weight of
+    W_up, by about 2^-12 of their h, meet opposite rows of W_down.  An h carries
+    some 2^-23 of its fp32 sums, 2^-11 of the difference; two planes would round
+    it by 2^-19 (root mean square), 2^-7 of it."""
+    P = _P()
+    w, x, _ = _inputs(d, m, B, d + 2 * B)
+    w = [v.clone() for v in w]
+    for i in range(2):
+        w[i][1::2] = w[i][0::2]
+    w[1][0::2, 5], w[1][1::2, 5] = 0.0, 2.0 ** (-12 if d < 2048 else -11)
+    w[2][1::2] = -w[2][0::2]
+    x64 = x.double()
+    h = _silu(x64 @ w[0].double().t()) * (x64 @ w[1].double().t())
+    want = h @ w[2].double()
+    two = _rel(_two_planes(h.float()) @ w[2].double(), want)
+    got = _rel(P.mlp_dense(P.Layer(*w), x), want)
+    print(f"[planes] h {d}x{m} B{B}: {got:.2e}, two planes {two:.2e}")
+    assert got <= 2.0 ** -9 and two >= 2.0 ** -7
 
 
 @pytest.mark.parametrize("d,m,B", [(1032, 3000, 8), (1032, 3000, 16), (5128, 700, 4)])

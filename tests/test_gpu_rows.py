@@ -90,7 +90,8 @@ def test_calibrate_stack_rows(d, m, N, L):
 
 
 def test_calibrate_stack_rows_keeps_inf_and_nan():
-    """Three planes: an infinite channel makes what fp32 products make of it."""
+    """An infinite channel makes of the vector what it makes of it in fp32: the
+    norm in front turns it into NaN."""
     P = _P()
     w = _layers(264, 31, 2, 9)
     x = torch.randn((20, 264), device="cuda")
@@ -134,3 +135,38 @@ def test_calibrate_stack_rows_infinite_weight():
             # (one neuron of 693 moves the middle rank by at most N places)
             assert t[1] == pytest.approx(plain[1], rel=1e-2)
             assert all(math.isnan(v) for v in t[2:])
+
+
+@pytest.mark.parametrize("d,m,N", [(1032, 31, 2), (512, 31, 3)])
+def test_calibrate_stack_rows_three_planes(d, m, N):
+    """All 24 bits of x count where three planes are taken (a width or a last
+    group of rows that had fp32 products): neighbouring channels of nearly equal
+    values meet opposite weights, so an activation is what the low bits differ
+    by, 2^-12 of a term.  The norm's and the sums' fp32 roundings are 2^-24 of a
+    partial sum of some sqrt(d) = 2^5 terms in 2^5 steps, so about 2^-12 of the
+    result and 2^-10 at most; two planes round each x by 2^-19 (root mean
+    square), 2^-7 of the result."""
+    P = _P()
+    g = torch.Generator(device="cuda").manual_seed(d + N)
+    r = torch.rand((N, d // 2), generator=g, device="cuda") + 0.5
+    x = torch.empty((N, d), device="cuda")
+    x[:, 0::2] = r
+    x[:, 1::2] = r - r * 2.0 ** -12 * (1 + torch.rand(r.shape, generator=g, device="cuda"))
+    half = (torch.randn((m, d // 2), generator=g, device="cuda") * 64).bfloat16()
+    wg = torch.empty((m, d), dtype=torch.bfloat16, device="cuda")
+    wg[:, 0::2], wg[:, 1::2] = half, -half
+    other = (torch.randn((m, d), generator=g, device="cuda") * 0.05).bfloat16()
+    stack = P.Stack([P.Layer(wg, other, other)])
+
+    def acts(z):
+        return _acts64(z, wg).reshape(-1).sort().values
+
+    xn = x.double() / torch.sqrt((x.double() ** 2).mean(dim=1, keepdim=True) + EPS)
+    hi = xn.float().bfloat16().float()
+    want, two = acts(xn), acts(hi.double() + (xn.float() - hi).bfloat16().double())
+    n = N * m
+    got = torch.tensor([P.calibrate_stack(stack, x, (i + 1) / n, eps=EPS)[0] for i in range(n)], dtype=torch.float64,
+                       device="cuda")
+    err, err2 = ((got - want).norm() / want.norm()).item(), ((two - want).norm() / want.norm()).item()
+    print(f"[planes] calibration {d}x{m} N{N}: {err:.2e}, two planes {err2:.2e}")
+    assert err <= 2.0 ** -10 and err2 >= 2.0 ** -8
