@@ -40,7 +40,15 @@
  *    a call starts (leftovers of other calls or entry points included);
  *    the arrival counters some kernels keep there are tagged per call.
  *  - x, y, residual, thresholds and calibration inputs are fp32.  Weights
- *    are CATS_F32 or CATS_BF16; all arithmetic accumulates in fp32.
+ *    are CATS_F32 or CATS_BF16; all arithmetic accumulates in fp32.  Calls
+ *    with bf16 weights that run on the matrix cores (several rows of a forward,
+ *    dense or stack call, by size; calibration) multiply an fp32 operand as two
+ *    or three bf16 parts, 16 or all 24 of its significand bits, each product
+ *    exact.  With three parts infinities and NaN in x give what fp32 products
+ *    give, and so do those in the weights, but that the calibration makes NaN of
+ *    an infinite weight's activations.  A batch multiplies the rows of W_down
+ *    that some row keeps with h = 0 for the rows that do not, so an infinite
+ *    weight there makes NaN of those too.
  *  - Weight layout is neuron-major: W_gate^T and W_up^T are stored [m x d]
  *    (row j holds neuron j's d input weights contiguously, the paper's
  *    "column-major W_up"), W_down is [m x d] row-major as in Eq. 1.  Use
@@ -123,7 +131,12 @@ const char* cats_last_error(void);
  * `max_batch` rows per forward, dense or stack call and up to `max_calib_values`
  * calibration activations (N * m) per calibration call (0 if calibration
  * is not used).  Pure host arithmetic, no HIP call.  Returns 0 for
- * arguments outside the supported range. */
+ * arguments outside the supported range.  For calibration that is 4 N (m + d)
+ * bytes and some: the activations, the vectors as two bf16 parts and the
+ * select's histograms.  cats_calibrate_threshold also takes 4 N m bytes and
+ * 1280, with kernels that split the vectors in every block and select in four
+ * passes: half as fast with bf16 weights (fp32 layers, whose products need no
+ * parts, lose the faster select alone). */
 size_t cats_workspace_bytes(int32_t d, int32_t m, int32_t max_batch, int64_t max_calib_values);
 
 /* Transpose a row-major [rows x cols] matrix into [cols x rows]
@@ -148,7 +161,9 @@ cats_status cats_calib_activations(const cats_layer* layer, const float* x, int3
  * smallest |a|, r = ceil(k*n - 1e-6) clamped to [1, n], which is
  * min{t' : F(t') >= k} for the empirical CDF F.  k = sparsity in [0, 1];
  * k = 0 gives t = 0 without touching the device.  Selection is exact (a
- * radix select on the fp32 bit patterns).  Synchronises `stream`. */
+ * radix select on the fp32 bit patterns).  `ws` is 1280 bytes or more; with
+ * 16640 the values are read three times instead of four, with wider loads.
+ * Synchronises `stream`. */
 cats_status cats_threshold_from_acts(const float* acts, int64_t n, double sparsity,
                                      void* ws, size_t ws_bytes, void* stream, float* t_out);
 
@@ -167,8 +182,9 @@ cats_status cats_calibrate_threshold(const cats_layer* layer, const float* calib
  * for B rows x (dev [B x d]); y (dev [B x d]); residual dev [B x d] or
  * NULL.  t >= 0 (t = +inf masks everything, y = residual or 0); each row
  * has its own Mask, and the rows of W_up / W_down read are the union of
- * the rows' masks.  Only the active rows of W_up and W_down are read.
- * aux may be NULL.  y must not alias x.  Enqueue only. */
+ * the rows' masks.  Only the active rows of W_up and W_down are read.  Two
+ * launches per pass of up to 8 rows, or three for all rows on the matrix
+ * cores (bf16, by size).  aux may be NULL.  y must not alias x.  Enqueue only. */
 cats_status cats_mlp_forward(const cats_layer* layer, const float* x, int32_t B, float t,
                              const float* residual, float* y, const cats_forward_aux* aux,
                              void* ws, size_t ws_bytes, void* stream);
@@ -201,7 +217,7 @@ cats_status cats_mlp_dense(const cats_layer* layer, const float* x, int32_t B,
  * the MLP blocks, Section 4; norms and residuals are outside its formulas,
  * Appendix B).  For l = 0 .. L-1:
  *   x_{l+1} = x_l + MLP_l(RMSNorm(x_l))
- * with unit-gain RMSNorm of epsilon eps (computed inside the fused kernel)
+ * with unit-gain RMSNorm of epsilon eps (computed inside the block's kernels)
  * and MLP_l the CATS forward of layers[l] at threshold t[l] (host array of
  * L values, each >= 0), or the dense MLP for every layer when t is NULL.
  *   layers   host array of L blocks (1 <= L <= CATS_MAX_LAYERS), one d for
@@ -213,7 +229,7 @@ cats_status cats_mlp_dense(const cats_layer* layer, const float* x, int32_t B,
  *   aux      host array of L cats_forward_aux (layer l's outputs for its
  *            MLP, as in cats_mlp_forward) or NULL; needs t
  * Workspace: cats_workspace_bytes(d, the largest m, B, 0).  Enqueue only;
- * two launches per layer on `stream`. */
+ * per layer the launches of a forward. */
 cats_status cats_stack_forward(const cats_layer* layers, int32_t L, const float* t,
                                const float* x0, int32_t B, float eps, float* x_out,
                                float* x_all, const cats_forward_aux* aux, void* ws,
@@ -250,9 +266,10 @@ cats_status cats_mlp_forward_topk(const cats_layer* layer, const float* x, int32
  *   mode CATS_UNFUSED_INDEX: the gate pass also writes each block's
  *        ascending list of the neurons active in some row (compacted without
  *        atomics), and the up and down kernels visit only those.
- * Both compute exactly what cats_mlp_forward computes (same t semantics,
- * fp32 accumulation); the fused forward is the product path, this entry
- * point exists to measure the paper's structure.  Arguments as
+ * Both compute what cats_mlp_forward computes (same t semantics, fp32
+ * accumulation), bit for bit where that call runs the fused kernel and to
+ * rounding where it runs on the matrix cores; the forward is the product path,
+ * this entry point exists to measure the paper's structure.  Arguments as
  * cats_mlp_forward (no aux outputs).  Workspace:
  * cats_unfused_workspace_bytes(d, m, B).  Enqueue only. */
 #define CATS_UNFUSED_MASK 0
@@ -295,8 +312,14 @@ cats_status cats_sparse_input_gemv(const void* w, int32_t d, int32_t n, int32_t 
  *   x_{l+1}  = x_l + dense MLP_l(RMSNorm(x_l))
  * t_out is a host array of L floats.  k = 0 gives t = 0 for every layer
  * without touching the device.  Workspace:
- * cats_calibrate_stack_workspace_bytes(d, largest m, N).  Synchronises
- * `stream` (once per layer).  Offline. */
+ * cats_calibrate_stack_workspace_bytes(d, largest m, N), which is
+ * 10 N (m + d) bytes and some: the activations, the vectors, and the vectors
+ * and h as three bf16 parts, so that each layer's products take all vectors
+ * at once (bf16 layers).  With 4 N m + 8 N d bytes and 1280 (or, if larger,
+ * cats_workspace_bytes(d, m, 16, 0) + 8 N d; each term rounded up to 256 bytes)
+ * the call propagates 16 vectors at a time, as it does for fp32 layers, which
+ * need no more than that: about eight times as slow.  Synchronises `stream`
+ * (once; 16 at a time, once per layer).  Offline. */
 size_t cats_calibrate_stack_workspace_bytes(int32_t d, int32_t max_m, int32_t N);
 cats_status cats_calibrate_stack(const cats_layer* layers, int32_t L, const float* calib_x,
                                  int32_t N, double sparsity, float eps, void* ws,

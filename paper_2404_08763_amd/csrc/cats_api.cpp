@@ -897,8 +897,9 @@ size_t stack_calib_general(int d, int max_m, int N) {
 
 // Workspace of the many-row propagation: the activations (later the
 // down-projection's partial sums, which need one [N x d] at least), X, then the
-// planes of RMSNorm(X) and of h, and the select's histograms and results.  A
-// workspace that holds the row groups' layout but not this one still works.
+// planes of RMSNorm(X) and of h, and the select's histograms and results.  Three
+// planes whatever N takes, so that a workspace for N vectors serves any fewer.
+// A workspace that holds the row groups' layout but not this one still works.
 struct StackCalibLayout {
   size_t acts, acts_bytes, X, xs, hs, hist, end;
 };
@@ -927,9 +928,10 @@ size_t cats_calibrate_stack_workspace_bytes(int32_t d, int32_t max_m, int32_t N)
 }
 
 namespace {
-// cats_calibrate_stack for bf16 layers and enough vectors: every layer's
-// products take all N vectors in one launch each.  Nothing is read back
-// until the last layer's cutoff is found.
+// cats_calibrate_stack for bf16 layers and any number of vectors, in a
+// workspace that holds stack_calib_layout: every layer's products take all N
+// vectors in one launch each.  Nothing is read back until the last layer's
+// cutoff is found.
 cats_status calibrate_stack_rows(const cats_layer* layers, int L, const float* calib_x, int N, double sparsity, float eps,
                                  int ns, const StackCalibLayout& lay, void* ws, hipStream_t s, float* t_out) {
   char* w = static_cast<char*>(ws);
@@ -1023,9 +1025,12 @@ cats_status cats_calibrate_stack(const cats_layer* layers, int32_t L, const floa
   cats_status st = check_ws(ws, ws_bytes, general + 2 * rows);
   if (st != CATS_OK) return st;
   const hipStream_t s = static_cast<hipStream_t>(stream);
-  // Two planes where the 16-row groups use two in every call; three, all of
-  // fp32's bits, where some group's products run on fp32 x (a width the
-  // matrix-core kernels lack, or a last group below their fewest rows).
+  // bf16 planes of the vectors in the many-row products.  Propagated 16 at a
+  // time, all vectors of a two-plane width but a last group of 1 to 4 were
+  // multiplied as two planes, that group as fp32 x; every other width was fp32
+  // x throughout.  No vector is multiplied with fewer bits than that here, and
+  // the products take all vectors alike, so such a last group makes it three
+  // planes for all (half as many products again).
   const int tail_rows = N % CATS_MAX_BATCH;
   const int ns = cats::batch_planes(d, tail_rows == 0 ? CATS_MAX_BATCH : tail_rows);
   bool many = true;
