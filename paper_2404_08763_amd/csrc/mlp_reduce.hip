@@ -55,7 +55,10 @@ __global__ __launch_bounds__(kReduceThreads) void k_mlp_reduce(ReduceArgs a) {
   const int d4 = a.d >> 2;
   const int ncb = (d4 + reduce_cols(a.few) - 1) / reduce_cols(a.few);
   const int nred = a.sum_y ? a.B * ncb : 0;
-  if (a.t_dst && blockIdx.x == 0 && tid < a.t_n) a.t_dst[tid] = a.t_src[tid];
+  // behind the first block's sums (its first wave is in both forms to the end)
+  auto copy_t = [&] {
+    if (blockIdx.x == 0 && a.t_dst && tid < a.t_n) a.t_dst[tid] = a.t_src[tid];
+  };
 
   if ((int)blockIdx.x < nred && a.few) {
     // y[b, c] = residual[b, c] + (s_0 + s_1) + (s_2 + s_3), s_r = the sum over k
@@ -90,6 +93,7 @@ __global__ __launch_bounds__(kReduceThreads) void k_mlp_reduce(ReduceArgs a) {
         tot = f32x4{__uint_as_float(rv.x), __uint_as_float(rv.y), __uint_as_float(rv.z), __uint_as_float(rv.w)} + tot;
       reinterpret_cast<f32x4*>(a.y + (size_t)b * a.d)[c4] = tot;
     }
+    copy_t();
     return;
   }
   if ((int)blockIdx.x < nred) {
@@ -131,6 +135,7 @@ __global__ __launch_bounds__(kReduceThreads) void k_mlp_reduce(ReduceArgs a) {
       }
       reinterpret_cast<f32x4*>(a.y + (size_t)b * a.d)[c4] = tot;
     }
+    copy_t();
     return;
   }
 
