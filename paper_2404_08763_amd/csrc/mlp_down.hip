@@ -192,12 +192,17 @@ __global__ __launch_bounds__(kDnThreads) void k_mlp_down(DownArgs a) {
   }
 
   // the two halves of the steps, in order
-  auto total = [&](int t) -> f32x4 { return NS == 3 ? add_lower_planes(acch[t], accl[t]) : acch[t] + accl[t]; };
+  if constexpr (NS == 3) {
+    add_lower_planes(acch, accl);
+  } else {
+#pragma unroll
+    for (int t = 0; t < 8; ++t) accl[t] = acch[t] + accl[t];
+  }
   __syncthreads();
   f32x4* red = reinterpret_cast<f32x4*>(s_w);
   if (wr == 1) {
 #pragma unroll
-    for (int t = 0; t < 8; ++t) red[(wc * 8 + t) * kWaveSize + lane] = total(t);
+    for (int t = 0; t < 8; ++t) red[(wc * 8 + t) * kWaveSize + lane] = accl[t];
   }
   __syncthreads();
   if (wr == 1) return;
@@ -209,7 +214,7 @@ __global__ __launch_bounds__(kDnThreads) void k_mlp_down(DownArgs a) {
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
       const int c = col0 + t * 16 + c4;
-      if (c < d) *reinterpret_cast<f32x4*>(part + c) = total(t) + red[(wc * 8 + t) * kWaveSize + lane];
+      if (c < d) *reinterpret_cast<f32x4*>(part + c) = accl[t] + red[(wc * 8 + t) * kWaveSize + lane];
     }
   }
 }

@@ -285,10 +285,16 @@ __global__ __launch_bounds__((GuGeom<T, NS, XR>::THREADS)) void k_mlp_gateup(Gat
     wait_lds();
     __syncthreads();                     // nor any other wave's
     f32x4* red = reinterpret_cast<f32x4*>(s0);
+    if constexpr (NS == 3) {
+      f32x4 first[T];
 #pragma unroll
-    for (int t = 0; t < T; ++t) {
-      const f32x4 first = acc[t][0] + acc[t][1];
-      red[(w * T + t) * kWaveSize + lane] = NS == 3 ? add_lower_planes(first, acl[t]) : first + acl[t];
+      for (int t = 0; t < T; ++t) first[t] = acc[t][0] + acc[t][1];
+      add_lower_planes(first, acl);
+#pragma unroll
+      for (int t = 0; t < T; ++t) red[(w * T + t) * kWaveSize + lane] = acl[t];
+    } else {
+#pragma unroll
+      for (int t = 0; t < T; ++t) red[(w * T + t) * kWaveSize + lane] = (acc[t][0] + acc[t][1]) + acl[t];
     }
     if (sq) {
       // the four lanes of a row, then the waves, in a fixed order
