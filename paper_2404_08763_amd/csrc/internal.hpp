@@ -110,8 +110,9 @@ hipError_t launch_fused_f32_cats(int nch, int bt, const FusedArgs& a, int G, hip
 hipError_t launch_fused_f32_cats_aux(int nch, int bt, const FusedArgs& a, int G, hipStream_t s);
 hipError_t launch_fused_f32_dense(int nch, int bt, const FusedArgs& a, int G, hipStream_t s);
 hipError_t launch_reduce(ReduceArgs a, hipStream_t s);
-// Whether the sum of G partials of that many outputs takes 16 columns per wave.
-bool reduce_few(int G, int outputs);
+// Whether the sum of G partials (of neuron groups where Gseg blocks listed the
+// neurons, G < Gseg) of that many outputs takes 16 columns per wave.
+bool reduce_few(int G, int Gseg, int outputs);
 
 // Top-k variant: gate activations of B <= 8 rows into v [B x m], the per-row
 // cutoffs (rank r of |v| within each row) into t [B], then the fused kernel

@@ -25,16 +25,21 @@ constexpr int kReduceFew = 64;
 constexpr int kReduceFewCols = kReduceThreads / 4;
 __host__ __device__ constexpr int reduce_cols(int few) { return few ? kReduceFewCols : kReduceWaves; }
 
-// Many outputs: from 16384 on, where a column per wave takes two blocks per
-// compute unit and more.  Below that its blocks are all on the chip at once,
-// each lane with one load to wait for, where the 16-column form has a
-// sixteenth of the blocks and 16 loads a lane (us a call, one column / 16
-// columns per wave: 1032 x 64 at 1 / 3 rows 6.8 / 7.6 and 10.3 / 11.0,
-// 4096 x 64 at 3 rows 14.6 / 15.3, 3072 x 1000 at 5 rows 19.9 / 20.3; at
-// 16384 outputs, 2048 x 1000 at 8 rows, 18.7 / 18.8; above, 2304 x 1000 at 8
-// rows 22.6 / 22.0, 4096 x 1000 at 5 rows 23.1 / 22.2, 8192 x 40 at 3 rows
-// 23.1 / 22.5).
-bool reduce_few(int G, int outputs) { return G <= kReduceFew && outputs >= 16384; }
+// Many outputs: more than 16384, two blocks of the one-column form per compute
+// unit.  Up to there all its blocks start at once, each lane with one load to
+// wait for, where the 16-column form has a sixteenth of the blocks and 16
+// loads a lane; beyond, its last blocks wait for the first (us a call, one column
+// / 16 columns per wave: 1032 x 64 at 1 / 3 rows 6.8 / 7.6 and 10.3 / 11.0,
+// 4096 x 64 at 3 rows 14.6 / 15.3, 2560 x 1500 at 6 rows 22.2 / 22.8; above,
+// 4104 x 20 at 4 rows 17.2 / 16.8, 2048 x 1500 at 9 rows 20.8 / 19.6, 5640 x 64 at
+// 3 rows 23.5 / 22.7, 5120 x 8000 at 5 rows 51.3 / 50.2).  At just 16384 the fused
+// kernel's partials by one column (8192 x 20 at 2 rows 14.7 / 15.0), neuron
+// groups' (fewer than the blocks that listed the neurons) by 16 (4096 x 11008 at 4
+// rows 50.9 / 50.4, 4096 x 20000 87.2 / 86.7, 2048 x 1500 at 8 rows 19.9 / 19.6,
+// but 2048 x 8000 32.0 / 32.2).
+bool reduce_few(int G, int Gseg, int outputs) {
+  return G <= kReduceFew && (G < Gseg ? outputs >= 16384 : outputs > 16384);
+}
 // List finalize: entries per thread per pass, and one count per wave and
 // entry slot, which one wave scans.
 constexpr int kFinPer = 8;
@@ -250,7 +255,7 @@ __global__ __launch_bounds__(kReduceThreads) void k_mlp_reduce(ReduceArgs a) {
 }
 
 hipError_t launch_reduce(ReduceArgs a, hipStream_t s) {
-  a.few = reduce_few(a.G, a.B * a.d) ? 1 : 0;
+  a.few = reduce_few(a.G, a.Gseg, a.B * a.d) ? 1 : 0;
   const int d4 = a.d >> 2;
   const int ncb = (d4 + reduce_cols(a.few) - 1) / reduce_cols(a.few);
   const int grid = (a.sum_y ? a.B * ncb : 0) + (a.aux ? a.B * fin_blocks(a.m) : 0);

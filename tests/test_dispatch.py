@@ -18,17 +18,19 @@ def _rule(symbol, *types):
 I = ctypes.c_int
 
 
-# d, partials, rows, us with one column / 16 columns per wave
-@pytest.mark.parametrize("d,G,B,one,sixteen", [
-    (1032, 64, 1, 6.8, 7.6), (1032, 16, 3, 9.8, 10.4), (512, 64, 3, 8.1, 8.7), (4096, 64, 3, 14.6, 15.3),
-    (4096, 8, 1, 7.5, 8.0), (8192, 32, 1, 9.7, 10.4), (3072, 42, 5, 19.9, 20.3),
-    (2304, 56, 8, 22.6, 22.0), (4096, 32, 5, 23.1, 22.2), (8192, 16, 8, 39.5, 36.0), (5120, 25, 16, 31.0, 26.8),
-    (2048, 64, 16, 21.3, 19.6),
+# d, partials, blocks that listed the neurons, rows, us with one column / 16 columns per wave
+@pytest.mark.parametrize("d,G,Gseg,B,one,sixteen", [
+    (1032, 64, 64, 1, 6.8, 7.6), (1032, 16, 16, 3, 9.8, 10.4), (512, 64, 64, 3, 8.1, 8.7), (4096, 64, 64, 3, 14.6, 15.3),
+    (4096, 8, 8, 1, 7.5, 8.0), (8192, 32, 32, 1, 9.7, 10.4), (3072, 42, 256, 5, 19.9, 20.3),
+    (2560, 47, 256, 6, 22.2, 22.8), (8192, 20, 20, 2, 14.7, 15.0), (4096, 32, 256, 4, 50.9, 50.4),
+    (4104, 20, 20, 4, 17.2, 16.8), (2048, 47, 256, 9, 20.8, 19.6), (2304, 56, 256, 8, 22.6, 22.0),
+    (4096, 32, 256, 5, 23.1, 22.2), (8192, 16, 256, 8, 39.5, 36.0), (5120, 25, 256, 16, 31.0, 26.8),
+    (2048, 64, 256, 16, 21.3, 19.6),
 ])
-def test_sum_of_few_partials(d, G, B, one, sixteen):
-    few = _rule("_ZN4cats10reduce_fewEii", I, I)
-    assert few(G, B * d) == (sixteen < one)
-    assert not few(65, B * d)
+def test_sum_of_few_partials(d, G, Gseg, B, one, sixteen):
+    few = _rule("_ZN4cats10reduce_fewEiii", I, I, I)
+    assert few(G, Gseg, B * d) == (sixteen < one)
+    assert not few(65, 256, B * d)
 
 
 @pytest.mark.parametrize("dense", [False, True])

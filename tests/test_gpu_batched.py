@@ -40,8 +40,8 @@ SHAPES = [
     (1024, 28672, 5),
     (2048, 32800, 7),    # its widest, CATS only, more than eight tiles
     (512, 65536, 16),    # the most neurons
-    (2048, 1000, 8),     # the sum of few partials at its fewest outputs
-    (2040, 1000, 8),     # and one column per wave below them
+    (2048, 1000, 8),     # the sum of few partials by 16 columns per wave, at its fewest outputs
+    (2040, 1000, 8),     # and by one column, at nearly its most
 ]
 
 
