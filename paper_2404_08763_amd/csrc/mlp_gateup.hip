@@ -1,5 +1,5 @@
 // Gate and up projections of a batch (3..16 rows, bf16 weights, any width) on
-// the matrix cores.
+// the matrix cores (narrow blocks of many neurons: mlp_gateup_narrow.hip).
 //
 //   v_bj = SiLU(x_b . W_gate[:, j]);  (b, j) active when |v_bj| >= t
 //   h_bj = v_bj * (x_b . W_up[:, j])  for active (b, j), else 0
